@@ -1,0 +1,442 @@
+"""The work that a user has this library do, as cases that can be timed.
+
+Six kinds of call, each through the package's public entry points:
+
+  product   y = A x in one of the storage schemes (a solver's inner step)
+  multi     Y = A X for k column-major vectors (block solvers)
+  batched   y_m = A_m x_m for many matrices in one launch
+  train     loss, gradients and a weight update through the Chebyshev recurrence
+  build     COO triplets -> CRS and its launch plan (assembly)
+  convert   CRS -> JDS -> blocked JDS, and JDS -> CRS
+
+The matrices are the repository's synthetic families (a 7-point stencil, power
+law rows, full diagonals, a Hamiltonian-shaped pattern, a band with a few far
+entries, uniform rows), drawn on the GPU from the seed.
+"""
+import math
+
+import numpy as np
+import torch
+
+import paper_0910_4836_amd as sp
+from paper_0910_4836_amd import autograd as sp_autograd
+
+DTYPES = {"f64": torch.float64, "f32": torch.float32, "bf16": torch.bfloat16}
+SIZE = {"f64": 8, "f32": 4, "bf16": 2}
+POWER = 1.6929      # row lengths L ~ L^-POWER on [1, LMAX]
+LMAX = 2000
+BAND = 1000
+PAIRS = 12          # mirrored diagonal pairs of "diagonals"
+OUTER = 6           # mirrored outer diagonal pairs of "hamiltonian"
+FILL = 0.7
+CHEB_STEPS = 20
+RATE = 1e-3
+
+
+def listed():
+    return [
+        # the smallest call: a 20^3 Laplacian, where latency and launches are all there is
+        {"name": "crs stencil", "kind": "product", "form": "crs", "pattern": "stencil", "n": 20, "val": "f64", "vec": "f64"},
+        # the three products of the headline step, at its size
+        {"name": "crs power law", "kind": "product", "form": "crs", "pattern": "power", "n": 2_000_000, "val": "f64", "vec": "f64"},
+        {"name": "jds power law", "kind": "product", "form": "jds_tiled", "pattern": "power", "n": 2_000_000, "val": "f64", "vec": "f64"},
+        # an ordinary, odd size in single precision: one of eight row blocks of that matrix
+        {"name": "blocked power law", "kind": "product", "form": "blocked_tiled", "pattern": "power", "n": 250_001, "val": "f32", "vec": "f32"},
+        # the large streaming matrix with its values stored in 16 bits
+        {"name": "jds diagonals", "kind": "product", "form": "jds", "pattern": "diagonals", "n": 6_000_000, "val": "bf16", "vec": "f32"},
+        # the Hamiltonian the storage schemes are meant for, in its best form
+        {"name": "dia hamiltonian", "kind": "product", "form": "dia", "pattern": "hamiltonian", "n": 6_000_000, "val": "f64", "vec": "f64"},
+        # block solvers: eight vectors, and a ragged count of them in single precision
+        {"name": "crs 8 vectors", "kind": "multi", "form": "crs", "pattern": "power", "n": 2_000_000, "k": 8, "val": "f64", "vec": "f64"},
+        {"name": "jds 13 vectors", "kind": "multi", "form": "jds", "pattern": "power", "n": 1_000_003, "k": 13, "val": "f32", "vec": "f32"},
+        # many matrices of 1e3 to 2e5 rows in one launch
+        {"name": "batched", "kind": "batched", "count": 128, "low": 1000, "high": 200_000},
+        # one training step: 20 Chebyshev steps forward, the reverse sweep, the update
+        {"name": "chebyshev step", "kind": "train", "pattern": "banded", "n": 4_000_000, "val": "f32", "vec": "f32"},
+        # assembly from unordered triplets with repeated positions
+        {"name": "build crs", "kind": "build", "pattern": "power", "n": 2_000_000, "shuffled": True, "val": "f64"},
+        # the storage schemes built from CRS, and CRS read back
+        {"name": "convert", "kind": "convert", "pattern": "power", "n": 2_000_000, "height": 64, "val": "f64"},
+    ]
+
+
+def _log(rng, low, high):
+    return int(math.exp(rng.uniform(math.log(low), math.log(high))))
+
+
+def draw(rng):
+    kind = rng.choice(["product"] * 6 + ["multi"] * 3 + ["batched", "train", "build", "build", "convert", "convert"])
+    prec = rng.choice([("f64", "f64"), ("f64", "f64"), ("f32", "f32"), ("f32", "f32"), ("bf16", "f32")])
+    if kind == "product":
+        pattern = rng.choice(["stencil", "power", "power", "diagonals", "hamiltonian", "banded", "uniform"])
+        forms = ["crs", "crs", "crs_staged", "jds", "jds_tiled", "blocked", "blocked_tiled", "windowed"]
+        if pattern in ("stencil", "diagonals", "hamiltonian"):
+            forms += ["dia", "dia"]
+        n = _log(rng, 12, 160) if pattern == "stencil" else _log(rng, 5_000, 4_000_000)
+        return {"kind": kind, "form": rng.choice(forms), "pattern": pattern, "n": n, "val": prec[0], "vec": prec[1]}
+    if kind == "multi":
+        return {"kind": kind, "form": rng.choice(["crs", "crs", "jds", "windowed"]),
+                "pattern": rng.choice(["power", "power", "banded", "uniform"]), "n": _log(rng, 5_000, 1_500_000),
+                "k": _log(rng, 2, 33), "val": prec[0], "vec": prec[1]}
+    if kind == "batched":
+        return {"kind": kind, "count": _log(rng, 4, 129), "low": 1000, "high": _log(rng, 4_000, 200_000)}
+    if kind == "train":
+        vec = rng.choice(["f64", "f32", "f32"])
+        return {"kind": kind, "pattern": rng.choice(["banded", "power"]), "n": _log(rng, 10_000, 1_500_000), "val": vec,
+                "vec": vec}
+    pattern = rng.choice(["stencil", "power", "power", "banded", "uniform"])
+    n = _log(rng, 12, 130) if pattern == "stencil" else _log(rng, 5_000, 2_000_000)
+    val = rng.choice(["f64", "f32"])
+    if kind == "build":
+        return {"kind": kind, "pattern": pattern, "n": n, "shuffled": rng.random() < 0.6, "val": val}
+    return {"kind": kind, "pattern": pattern, "n": n, "height": rng.choice([32, 64, 128, 256]), "val": val}
+
+
+# ------------------------------------------------------------------ patterns
+# How many entries a row has follows from the case alone, so that every seed
+# gives outputs of one shape; where they lie, and their values, from the seed.
+
+
+def _gen(seed, salt=0):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(int(seed) * 1000003 + salt)
+    return g
+
+
+def _below(g, high, count):
+    """`count` integers uniform in [0, high) for an integer or a tensor of them."""
+    u = torch.rand(count, generator=g, device="cuda", dtype=torch.float64)
+    return torch.minimum((u * high).long(), torch.as_tensor(high, device="cuda") - 1)
+
+
+def _length_weights(n):
+    w = np.arange(1, min(LMAX, n) + 1, dtype=np.float64) ** -POWER
+    return w / w.sum()
+
+
+def _lengths(pattern, n):
+    order = torch.randperm(n, generator=_gen(n, 7), device="cuda")
+    if pattern == "banded":
+        return torch.full((n,), 20, device="cuda")
+    if pattern == "uniform":
+        return 5 + order % 36
+    cdf = torch.tensor(np.cumsum(_length_weights(n)), device="cuda")
+    return 1 + torch.searchsorted(cdf, (order.double() + 0.5) / n).clamp(max=cdf.numel() - 1)
+
+
+def _distinct(g, rows, pos, count, width):
+    """Entry `pos` of `count` distinct ones in [0, width): one in each of `count` equal strata."""
+    low = torch.div(pos * width, count, rounding_mode="floor")
+    return low + _below(g, torch.div((pos + 1) * width, count, rounding_mode="floor") - low, rows.numel())
+
+
+def _rows_of(lengths):
+    rows = torch.repeat_interleave(torch.arange(lengths.numel(), device="cuda"), lengths)
+    return rows, torch.arange(rows.numel(), device="cuda") - (torch.cumsum(lengths, 0) - lengths)[rows]
+
+
+def _near_and_far(g, lengths, near, band):
+    """Rows of `lengths` entries, `near` of them within `band` of the diagonal and the others anywhere else."""
+    n = lengths.numel()
+    rows, pos = _rows_of(lengths)
+    low = (rows - band).clamp(min=0)
+    width = (rows + band).clamp(max=n - 1) - low + 1
+    close = near[rows]
+    inside = pos < close
+    cols = low + _distinct(g, rows, torch.where(inside, pos, 0), close, width)
+    far = _distinct(g, rows, torch.where(inside, 0, pos - close), (lengths[rows] - close).clamp(min=1), n - width)
+    return rows, torch.where(inside, cols, far + torch.where(far >= low, width, 0))
+
+
+def _offsets(n, low, high, count):
+    r = np.random.default_rng(n)
+    return [int(o) for o in np.sort(r.choice(np.arange(low, max(high, low + count)), size=count, replace=False))]
+
+
+def _sorted(rows, cols, n):
+    key = (rows * n + cols).sort()[0]
+    return torch.div(key, n, rounding_mode="floor"), key % n, n
+
+
+def _pattern(pattern, n, seed):
+    """(rows, cols, n): the pattern's positions as int64, by rows and columns, each once."""
+    g = _gen(seed)
+    if pattern == "stencil":
+        m, n = n, n ** 3
+        p = torch.arange(n, device="cuda")
+        z, y, x = p // (m * m), (p // m) % m, p % m
+        cols = torch.stack([p - m * m, p - m, p - 1, p, p + 1, p + m, p + m * m], 1)
+        keep = torch.stack([z > 0, y > 0, x > 0, p >= 0, x < m - 1, y < m - 1, z < m - 1], 1)
+        return p[:, None].expand(-1, 7)[keep], cols[keep], n
+    if pattern == "diagonals":
+        up = _offsets(n, 1, n // 4, PAIRS)
+        cols = torch.arange(n, device="cuda")[:, None] + torch.tensor([-o for o in up[::-1]] + [0] + up, device="cuda")
+        keep = (cols >= 0) & (cols < n)
+        return torch.arange(n, device="cuda")[:, None].expand(-1, 2 * PAIRS + 1)[keep], cols[keep], n
+    if pattern == "hamiltonian":
+        p = torch.arange(n, device="cuda")
+        r, c = [], []
+        for o in _offsets(n, min(1000, n // 8), n // 4, OUTER):
+            i = torch.randperm(n - o, generator=g, device="cuda")[:int(FILL * (n - o))]
+            r, c = r + [i], c + [i + o]
+        i, pos = _rows_of(torch.minimum(2 + (p % 10 < 3).long(), n - 1 - p))
+        j = i + 1 + _distinct(g, i, pos, torch.minimum(2 + (i % 10 < 3).long(), n - 1 - i), (n - 1 - i).clamp(max=500))
+        r, c = torch.cat(r + [i]), torch.cat(c + [j])
+        return _sorted(torch.cat([r, c, p]), torch.cat([c, r, p]), n)
+    lengths = _lengths(pattern, n)
+    if pattern == "uniform":
+        rows, pos = _rows_of(lengths)
+        return rows, _distinct(g, rows, pos, lengths[rows], n), n
+    if pattern == "banded":
+        return _sorted(*_near_and_far(g, lengths, lengths * 4 // 5, min(5000, n // 4)), n)
+    return _sorted(*_near_and_far(g, lengths, (lengths + 1) // 2, BAND), n)
+
+
+def _values(count, val, seed):
+    """`count` normal values that `val` holds exactly, as float64."""
+    if val == "f64":
+        return torch.randn(count, generator=_gen(seed, 1), device="cuda", dtype=torch.float64)
+    return torch.randn(count, generator=_gen(seed, 1), device="cuda").to(DTYPES[val]).double()
+
+
+def _vector(shape, vec, seed, salt=2):
+    return torch.rand(shape, generator=_gen(seed, salt), device="cuda", dtype=DTYPES[vec]) * 2 - 1
+
+
+def _matrix(case, seed):
+    rows, cols, n = _pattern(case["pattern"], case["n"], seed)
+    return rows, cols, _values(rows.numel(), case["val"], seed), n
+
+
+def _crs(rows, cols, vals, n, val):
+    """CRS as a program builds it: assembled in FP64 (or FP32), then rounded to the stored type."""
+    wide = torch.float32 if val == "f32" else torch.float64
+    A = sp.csr_from_coo(n, n, rows.int(), cols.int(), vals.to(wide))
+    return A.with_values(sp.spmv_convert_values(A.val, torch.bfloat16)) if val == "bf16" else A
+
+
+def _triplets(case, seed):
+    """COO triplets of `build`: the pattern's positions, one in twenty of them given twice."""
+    rows, cols, n = _pattern(case["pattern"], case["n"], seed)
+    m = rows.numel()
+    again = _below(_gen(seed, 5), m, m // 20)
+    at = torch.cat([torch.arange(m, device="cuda"), again])
+    at = at[torch.randperm(at.numel(), generator=_gen(seed, 6), device="cuda")] if case["shuffled"] else at.sort()[0]
+    return rows[at], cols[at], _values(at.numel(), case["val"], seed), n
+
+
+def _sizes(case):
+    r = np.random.default_rng(case["count"] * case["high"])
+    n = np.floor(np.exp(r.uniform(math.log(case["low"]), math.log(case["high"]), size=case["count"])))
+    return [int(v) for v in np.sort(n)[::-1]]
+
+
+def _batch(case, seed):
+    """(rows, cols, values, n) of each matrix of `batched`, rows of 5 to 40 entries."""
+    for m, n in enumerate(_sizes(case)):
+        rows, cols, n = _pattern("uniform", n, seed * 1009 + m)
+        yield rows, cols, _values(rows.numel(), "f32", seed * 1009 + m), n
+
+
+# ------------------------------------------------------------------ the calls
+
+
+def prepare(case, seed):
+    kind = case["kind"]
+    if kind == "build":
+        rows, cols, vals, n = _triplets(case, seed)
+        return {"kind": kind, "n": n, "rows": rows.int(), "cols": cols.int(), "vals": vals.to(DTYPES[case["val"]])}
+    if kind == "batched":
+        mats = [sp.jds_blocked_from_jds(sp.jds_from_csr(_crs(*m, "f32")), 64) for m in _batch(case, seed)]
+        B = sp.Batched(mats)
+        return {"kind": kind, "B": B, "x": _vector(B.total_cols, "f32", seed)}
+    rows, cols, vals, n = _matrix(case, seed)
+    if kind == "train":
+        vals = vals / torch.zeros(n, device="cuda", dtype=torch.float64).index_add_(0, rows, vals.abs()).max()
+    A = _crs(rows, cols, vals, n, case["val"])
+    del rows, cols, vals
+    if kind == "convert":
+        return {"kind": kind, "A": A, "height": case["height"]}
+    if kind == "train":
+        op = sp_autograd.SpMVOperator(A)
+        return {"kind": kind, "op": op, "vals": op.vals_from_crs(A.val).requires_grad_(),
+                "x": _vector(n, case["vec"], seed).requires_grad_()}
+    if kind == "multi":
+        x = _vector((case["k"], n), case["vec"], seed).t()
+        M = {"crs": sp.spmv_crs_plan, "jds": sp.jds_from_csr,
+             "windowed": lambda a: sp.jds_blocked_windowed_from_csr(a, 64, 16384)}[case["form"]](A)
+        return {"kind": kind, "form": case["form"], "M": M, "x": x}
+    form, M = case["form"], A
+    if form in ("crs", "crs_staged"):
+        M = sp.spmv_crs_plan(A)
+        M.staged = form == "crs_staged"
+    elif form in ("jds", "jds_tiled"):
+        M = sp.jds_from_csr(A)
+    elif form in ("blocked", "blocked_tiled"):
+        M = sp.jds_blocked_from_jds(sp.jds_from_csr(A), 64)
+    elif form == "windowed":
+        M = sp.jds_blocked_windowed_from_csr(A, 64, 65536)
+    else:
+        M = sp.dia_from_csr(A, sliced=True)
+    if form in ("blocked_tiled", "windowed"):
+        sp.spmv_jds_blocked_tiles(M)
+    if form == "jds_tiled":
+        sp.spmv_jds_tiles(M)
+    return {"kind": kind, "form": form, "M": M, "x": _vector(n, case["vec"], seed)}
+
+
+PRODUCT = {"crs": sp.spmv_crs, "crs_staged": sp.spmv_crs, "jds": sp.spmv_jds, "jds_tiled": sp.spmv_jds_tiled,
+           "blocked": sp.spmv_jds_blocked, "blocked_tiled": sp.spmv_jds_blocked_tiled,
+           "windowed": sp.spmv_jds_blocked_tiled, "dia": sp.spmv_dia}
+MULTI = {"crs": sp.spmm_crs, "jds": sp.spmm_jds, "windowed": sp.spmm_jds_blocked}
+
+
+def run(state):
+    kind = state["kind"]
+    if kind == "product":
+        return PRODUCT[state["form"]](state["M"], state["x"])
+    if kind == "multi":
+        return MULTI[state["form"]](state["M"], state["x"])
+    if kind == "batched":
+        return state["B"](state["x"])
+    if kind == "build":
+        A = sp.spmv_crs_plan(sp.csr_from_coo(state["n"], state["n"], state["rows"], state["cols"], state["vals"]))
+        return {"row_ptr": A.row_ptr, "col": A.col_idx, "val": A.val, "plan": A.plan}
+    if kind == "convert":
+        J = sp.jds_from_csr(state["A"])
+        B = sp.jds_blocked_from_jds(J, state["height"])
+        A = sp.jds_to_csr(J)
+        return {"perm": J.perm, "iperm": J.iperm, "jd_ptr": J.jd_ptr, "jd_col": J.jd_col, "jd_val": J.jd_val,
+                "slice_ptr": B.slice_ptr, "slice_nd": B.slice_nd, "bl_col": B.bl_col, "bl_val": B.bl_val,
+                "row_ptr": A.row_ptr, "col": A.col_idx, "val": A.val}
+    vals, x = state["vals"], state["x"]
+    vals.grad = x.grad = None
+    loss = sp_autograd.chebyshev_loss(state["op"], vals, x, CHEB_STEPS)
+    loss.backward()
+    with torch.no_grad():
+        vals.add_(vals.grad, alpha=-RATE)
+    # the loss is logged in the type that the states have
+    return {"loss": loss.detach().to(x.dtype), "dvals": vals.grad, "dx": x.grad, "vals": vals.detach()}
+
+
+# ------------------------------------------------------------------ what the work cannot do without
+
+
+def _count(case):
+    """Rows and stored entries that the pattern has (expected, where it is random)."""
+    n, pattern = case["n"], case["pattern"]
+    if pattern == "stencil":
+        return n ** 3, 7 * n ** 3 - 6 * n ** 2
+    if pattern == "diagonals":
+        return n, int(n * (1 + 2 * PAIRS * 7 / 8))
+    if pattern == "hamiltonian":
+        return n, int(n * (1 + 2 * OUTER * FILL * 7 / 8 + 4.6))
+    if pattern == "power":
+        w = _length_weights(n)
+        return n, int(n * float((w * np.arange(1, w.size + 1)).sum()))
+    return n, int(n * (20 if pattern == "banded" else 22.5))
+
+
+def work(case):
+    kind = case["kind"]
+    if kind == "batched":
+        span = math.log(case["high"] / case["low"])
+        n = int(case["count"] * (case["high"] - case["low"]) / span)
+        return {"bytes": n * 22.5 * 8 + n * 12, "flops": 2 * n * 22.5}
+    n, nnz = _count(case)
+    v = SIZE[case["val"]]
+    if kind == "build":
+        m = nnz * 21 // 20
+        return {"bytes": m * (8 + v) + nnz * (4 + v) + 4 * n, "flops": m}
+    if kind == "convert":
+        # CRS in; JDS, blocked JDS and CRS out
+        return {"bytes": 4 * nnz * (4 + v) + 16 * n, "flops": nnz}
+    x = SIZE[case["vec"]]
+    if kind == "multi":
+        return {"bytes": nnz * (4 + v) + 4 * n + 2 * n * case["k"] * x, "flops": 2 * nnz * case["k"]}
+    if kind == "train":
+        # each forward and transposed product reads the matrix and two or three vectors; the
+        # value gradient's sum over the steps and the update touch the values once each
+        product = nnz * (4 + v) + 4 * n + 3 * n * x
+        return {"bytes": 2 * CHEB_STEPS * product + CHEB_STEPS * 2 * n * x + 3 * nnz * v,
+                "flops": CHEB_STEPS * 6 * nnz + 2 * nnz}
+    if case["form"] == "dia":
+        far = {"stencil": 7, "diagonals": 1 + 2 * PAIRS, "hamiltonian": 1 + 2 * OUTER}[case["pattern"]]
+        rest = 4.6 if case["pattern"] == "hamiltonian" else 0
+        return {"bytes": int(n * (far * v + rest * (4 + v) + 2 * x)), "flops": 2 * nnz}
+    return {"bytes": nnz * (4 + v) + 4 * n + 2 * n * x, "flops": 2 * nnz}
+
+
+# ------------------------------------------------------------------ the same in 64 bits
+
+
+def _mul(rows, cols, vals, n, x):
+    """A x in float64, for a vector or a (n, k) block."""
+    y = torch.zeros((n, *x.shape[1:]), device="cuda", dtype=torch.float64)
+    step = max(1, (1 << 28) // (x[0].numel() if x.dim() > 1 else 1))
+    for a in range(0, rows.numel(), step):
+        v = vals[a:a + step]
+        y.index_add_(0, rows[a:a + step], (v[:, None] if x.dim() > 1 else v) * x[cols[a:a + step]])
+    return y
+
+
+def _jds_slots(rows, n):
+    """JDS slot of every entry (given by rows), and the permutation and row lengths behind it."""
+    length = torch.bincount(rows, minlength=n)
+    perm = torch.sort(length, descending=True, stable=True)[1]
+    iperm = torch.empty_like(perm).scatter_(0, perm, torch.arange(n, device="cuda"))
+    d = torch.arange(rows.numel(), device="cuda") - (torch.cumsum(length, 0) - length)[rows]
+    count = torch.bincount(d)
+    return (torch.cumsum(count, 0) - count)[d] + iperm[rows], d, iperm[rows], length[perm]
+
+
+def _exact_train(case, seed):
+    rows, cols, vals, n = _matrix(case, seed)
+    vals = vals / torch.zeros(n, device="cuda", dtype=torch.float64).index_add_(0, rows, vals.abs()).max()
+    vals = vals.to(DTYPES[case["val"]]).double()
+    y = [_vector(n, case["vec"], seed).double()]
+    y.append(_mul(rows, cols, vals, n, y[0]))
+    for k in range(1, CHEB_STEPS):
+        y.append(2 * _mul(rows, cols, vals, n, y[k]) - y[k - 1])
+    loss = torch.dot(y[-1], y[-1])
+    bar = [torch.zeros_like(y[0]) for _ in y]
+    bar[-1] = 2 * y[-1]
+    dvals = torch.zeros_like(vals)
+    for k in range(CHEB_STEPS - 1, -1, -1):
+        g = (2.0 if k else 1.0) * bar[k + 1]
+        bar[k] += _mul(cols, rows, vals, n, g)
+        if k:
+            bar[k - 1] -= bar[k + 1]
+        dvals += g[rows] * y[k][cols]
+    slot = _jds_slots(rows, n)[0]
+    put = lambda v: torch.empty_like(v).scatter_(0, slot, v)  # noqa: E731
+    return {"loss": loss, "dvals": put(dvals), "dx": bar[0], "vals": put(vals - RATE * dvals)}
+
+
+def exact(case, seed):
+    kind = case["kind"]
+    if kind == "train":
+        return _exact_train(case, seed)
+    if kind == "batched":
+        sizes = _sizes(case)
+        x = _vector(sum(sizes), "f32", seed).double().split(sizes)
+        return torch.cat([_mul(r, c, v, n, xm) for (r, c, v, n), xm in zip(_batch(case, seed), x)])
+    if kind == "build":
+        rows, cols, vals, n = _triplets(case, seed)
+        key, at = torch.unique(rows * n + cols, return_inverse=True)
+        val = torch.zeros(key.numel(), device="cuda", dtype=torch.float64).index_add_(0, at, vals)
+        return {"row_ptr": None, "col": None, "val": val, "plan": None}
+    rows, cols, vals, n = _matrix(case, seed)
+    if kind == "convert":
+        slot, d, at, length = _jds_slots(rows, n)
+        C = case["height"]
+        depth = length[::C] * C
+        start = torch.cumsum(depth, 0) - depth
+        s = torch.div(at, C, rounding_mode="floor")
+        bl = torch.zeros(int(depth.sum()), device="cuda", dtype=torch.float64)
+        bl[start[s] + d * C + at - s * C] = vals
+        none = dict.fromkeys(("perm", "iperm", "jd_ptr", "jd_col", "slice_ptr", "slice_nd", "bl_col", "row_ptr", "col"))
+        return {**none, "jd_val": torch.empty_like(vals).scatter_(0, slot, vals), "bl_val": bl, "val": vals}
+    if kind == "multi":
+        return _mul(rows, cols, vals, n, _vector((case["k"], n), case["vec"], seed).t().double())
+    return _mul(rows, cols, vals, n, _vector(n, case["vec"], seed).double())
