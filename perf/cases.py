@@ -89,7 +89,7 @@ def draw(rng):
     val = rng.choice(["f64", "f32"])
     if kind == "build":
         return {"kind": kind, "pattern": pattern, "n": n, "shuffled": rng.random() < 0.6, "val": val}
-    return {"kind": kind, "pattern": pattern, "n": n, "height": rng.choice([32, 64, 128, 256]), "val": val}
+    return {"kind": kind, "pattern": pattern, "n": n, "height": rng.choice([64, 128, 192, 256]), "val": val}
 
 
 # ------------------------------------------------------------------ patterns
