@@ -122,13 +122,27 @@ static spmv_status exclusive_scan(const TI *in, int64_t n, TO *out, TO *ws, hipS
 }
 
 // ================================================================ radix sort
-// Stable LSD radix sort of (uint32 key, int32 value) pairs, 8 bits per pass.
-
-constexpr int RS_THREADS = 256;
+// Stable LSD radix sort of uint32 keys with one or two payload arrays, 8 bits
+// per pass.  A pass reads and writes every item once, so its bound is the
+// copy rate; three kernels: per-tile digit counts, their scan (digit-major),
+// and the scatter.  The scatter orders its tile by digit in LDS first, so
+// that a digit's items leave as one run (8192 items / 256 digits: 128 bytes
+// of 4-byte items on average) instead of one 4-byte store per line, and it
+// issues all of a lane's loads before the first rank is taken.  Tiles are
+// dealt to the XCDs in contiguous ranges: neighbouring tiles append to the
+// same lines of every digit's run.
+constexpr int RS_THREADS = 512;
 constexpr int RS_WAVES = RS_THREADS / WAVE;
 constexpr int RS_ITEMS = 16;                       // per lane
-constexpr int RS_TILE = RS_THREADS * RS_ITEMS;     // 4096 keys per tile
+constexpr int RS_TILE = RS_THREADS * RS_ITEMS;     // 8192 items per tile
 constexpr int RS_BINS = 256;
+
+struct NoPayload {};
+
+template <typename V>
+struct PayloadSize { static constexpr size_t value = sizeof(V); };
+template <>
+struct PayloadSize<NoPayload> { static constexpr size_t value = 0; };
 
 __global__ __launch_bounds__(RS_THREADS) void radix_hist_kernel(const uint32_t *__restrict__ keys, int64_t n,
                                                                 int shift, int32_t *__restrict__ counts,
@@ -137,38 +151,71 @@ __global__ __launch_bounds__(RS_THREADS) void radix_hist_kernel(const uint32_t *
     __shared__ int32_t h[RS_BINS];
     for (int i = threadIdx.x; i < RS_BINS; i += RS_THREADS) h[i] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * RS_TILE;
+    const int64_t tile = xcd_remap(blockIdx.x, ntiles);
+    const int64_t base = tile * RS_TILE;
+    uint32_t k[RS_ITEMS];
+#pragma unroll
     for (int j = 0; j < RS_ITEMS; ++j) {
-        int64_t i = base + (int64_t)j * RS_THREADS + threadIdx.x;
-        if (i < n) atomicAdd(&h[(keys[i] >> shift) & 0xff], 1);
+        const int64_t i = base + (int64_t)j * RS_THREADS + threadIdx.x;
+        k[j] = i < n ? keys[i] : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < RS_ITEMS; ++j) {
+        const int64_t i = base + (int64_t)j * RS_THREADS + threadIdx.x;
+        if (i < n) atomicAdd(&h[((k[j] >> shift) & (RS_BINS - 1))], 1);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < RS_BINS; i += RS_THREADS) counts[(int64_t)i * ntiles + blockIdx.x] = h[i];
+    for (int i = threadIdx.x; i < RS_BINS; i += RS_THREADS) counts[(int64_t)i * ntiles + tile] = h[i];
 }
 
+// offs[d * ntiles + tile]: where tile's items of digit d start.  A first
+// payload of nullptr stands for the item's index.
+template <typename V1, typename V2>
 __global__ __launch_bounds__(RS_THREADS) void radix_scatter_kernel(const uint32_t *__restrict__ kin,
-                                                                   const int32_t *__restrict__ vin, int64_t n,
-                                                                   int shift, const int32_t *__restrict__ offs,
-                                                                   int64_t ntiles, uint32_t *__restrict__ kout,
-                                                                   int32_t *__restrict__ vout)
+                                                                   const V1 *__restrict__ vin,
+                                                                   const V2 *__restrict__ win, int64_t n, int shift,
+                                                                   const int32_t *__restrict__ offs, int64_t ntiles,
+                                                                   uint32_t *__restrict__ kout,
+                                                                   V1 *__restrict__ vout, V2 *__restrict__ wout)
 {
+    constexpr bool TWO = PayloadSize<V2>::value != 0;
+    constexpr size_t ITEM = PayloadSize<V1>::value > PayloadSize<V2>::value ? PayloadSize<V1>::value
+                                                                              : PayloadSize<V2>::value;
+    constexpr size_t SLOT = ITEM > sizeof(uint32_t) ? ITEM : sizeof(uint32_t);
+    __shared__ double buf[RS_TILE * SLOT / sizeof(double)];
     __shared__ int32_t cnt[RS_WAVES][RS_BINS];
-    for (int i = threadIdx.x; i < RS_WAVES * RS_BINS; i += RS_THREADS) (&cnt[0][0])[i] = 0;
-    __syncthreads();
-    const int w = (int)threadIdx.x / WAVE, lane = lane_id();
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (WAVE - lane));
-    // wave w owns keys [base_w, base_w + 64*RS_ITEMS), in rounds of 64 in order
-    const int64_t base_w = (int64_t)blockIdx.x * RS_TILE + (int64_t)w * WAVE * RS_ITEMS;
+    __shared__ int32_t gofs[RS_BINS];
+    __shared__ int32_t wtot[RS_BINS / WAVE];
+    const int t = (int)threadIdx.x, w = t / WAVE, lane = lane_id();
+    const int64_t tile = xcd_remap(blockIdx.x, ntiles);
+    const int64_t base = tile * RS_TILE;
+    const int32_t n_in = n - base < RS_TILE ? (int32_t)(n - base) : RS_TILE;
+    const int32_t first = t < RS_BINS ? offs[(int64_t)t * ntiles + tile] : 0;
+    // wave w owns items [1024 w, 1024 (w + 1)) of the tile, in rounds of 64 in order
+    const int32_t lw = w * WAVE * RS_ITEMS + lane;
     uint32_t k[RS_ITEMS];
-    int32_t v[RS_ITEMS];
+    V1 v[RS_ITEMS];
+    V2 x[RS_ITEMS];
+#pragma unroll
+    for (int j = 0; j < RS_ITEMS; ++j) {
+        const int32_t i = lw + j * WAVE;
+        k[j] = i < n_in ? kin[base + i] : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < RS_ITEMS; ++j) {
+        const int32_t i = lw + j * WAVE;
+        if (vin) v[j] = i < n_in ? vin[base + i] : V1(0);
+        else v[j] = (V1)(base + i);
+        if constexpr (TWO) x[j] = i < n_in ? win[base + i] : V2(0);
+    }
+    for (int i = t; i < RS_WAVES * RS_BINS; i += RS_THREADS) (&cnt[0][0])[i] = 0;
+    __syncthreads();
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (WAVE - lane));
     int32_t rank[RS_ITEMS];
 #pragma unroll
     for (int j = 0; j < RS_ITEMS; ++j) {
-        const int64_t i = base_w + (int64_t)j * WAVE + lane;
-        const bool in = i < n;
-        k[j] = in ? kin[i] : 0u;
-        v[j] = in ? vin[i] : 0;
-        const uint32_t dg = (k[j] >> shift) & 0xff;
+        const bool in = lw + j * WAVE < n_in;
+        const uint32_t dg = ((k[j] >> shift) & (RS_BINS - 1));
         uint64_t peers = __ballot(in);
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
@@ -183,70 +230,152 @@ __global__ __launch_bounds__(RS_THREADS) void radix_scatter_kernel(const uint32_
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    // per digit: exclusive prefix over the waves (tile order = wave order)
-    for (int dg = threadIdx.x; dg < RS_BINS; dg += RS_THREADS) {
-        int32_t run = 0;
+    // per digit: exclusive prefix over the waves (tile order = wave order),
+    // then over the digits
+    int32_t run = 0, inc = 0;
+    if (t < RS_BINS) {
+#pragma unroll
         for (int q = 0; q < RS_WAVES; ++q) {
-            int32_t c = cnt[q][dg];
-            cnt[q][dg] = run;
+            const int32_t c = cnt[q][t];
+            cnt[q][t] = run;
             run += c;
+        }
+        inc = run;
+        for (int off = 1; off < WAVE; off <<= 1) {
+            const int32_t o = __shfl_up(inc, off, WAVE);
+            if (lane >= off) inc += o;
+        }
+        if (lane == WAVE - 1) wtot[w] = inc;
+    }
+    __syncthreads();
+    if (t < RS_BINS) {
+        int32_t ds = inc - run;
+        for (int q = 0; q < w; ++q) ds += wtot[q];
+#pragma unroll
+        for (int q = 0; q < RS_WAVES; ++q) cnt[q][t] += ds;
+        gofs[t] = first - ds;
+    }
+    __syncthreads();
+    // through LDS into digit order: keys, then each payload
+    uint32_t *kb = reinterpret_cast<uint32_t *>(buf);
+#pragma unroll
+    for (int j = 0; j < RS_ITEMS; ++j) {
+        rank[j] += cnt[w][((k[j] >> shift) & (RS_BINS - 1))];
+        if (lw + j * WAVE < n_in) kb[rank[j]] = k[j];
+    }
+    __syncthreads();
+    int32_t pos[RS_ITEMS];
+#pragma unroll
+    for (int j = 0; j < RS_ITEMS; ++j) {
+        const int32_t i = j * RS_THREADS + t;
+        if (i < n_in) {
+            const uint32_t key = kb[i];
+            pos[j] = gofs[((key >> shift) & (RS_BINS - 1))] + i;
+            kout[pos[j]] = key;
         }
     }
     __syncthreads();
+    V1 *vb = reinterpret_cast<V1 *>(buf);
+#pragma unroll
+    for (int j = 0; j < RS_ITEMS; ++j)
+        if (lw + j * WAVE < n_in) vb[rank[j]] = v[j];
+    __syncthreads();
 #pragma unroll
     for (int j = 0; j < RS_ITEMS; ++j) {
-        const int64_t i = base_w + (int64_t)j * WAVE + lane;
-        if (i < n) {
-            const uint32_t dg = (k[j] >> shift) & 0xff;
-            const int64_t pos = (int64_t)offs[(int64_t)dg * ntiles + blockIdx.x] + cnt[w][dg] + rank[j];
-            kout[pos] = k[j];
-            vout[pos] = v[j];
+        const int32_t i = j * RS_THREADS + t;
+        if (i < n_in) vout[pos[j]] = vb[i];
+    }
+    if constexpr (TWO) {
+        __syncthreads();
+        V2 *xb = reinterpret_cast<V2 *>(buf);
+#pragma unroll
+        for (int j = 0; j < RS_ITEMS; ++j)
+            if (lw + j * WAVE < n_in) xb[rank[j]] = x[j];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < RS_ITEMS; ++j) {
+            const int32_t i = j * RS_THREADS + t;
+            if (i < n_in) wout[pos[j]] = xb[i];
         }
     }
+}
+
+static size_t radix_cells(int64_t n) { return (size_t)(n > 0 ? ceil_div(n, RS_TILE) : 1) * RS_BINS; }
+
+// counts, offsets and scan scratch of a pass
+static size_t radix_table_bytes(int64_t n)
+{
+    const size_t cells = radix_cells(n);
+    return align_up(sizeof(int32_t) * cells, 256) + align_up(sizeof(int32_t) * (cells + 1), 256) +
+           align_up(sizeof(int32_t) * scan_ws_elems((int64_t)cells), 256) + 256;
 }
 
 static size_t radix_ws_bytes(int64_t n)
 {
-    int64_t ntiles = n > 0 ? ceil_div(n, RS_TILE) : 1;
-    size_t cells = (size_t)ntiles * RS_BINS;
-    size_t b = 0;
-    b += align_up(sizeof(int32_t) * cells, 256);                 // counts
-    b += align_up(sizeof(int32_t) * (cells + 1), 256);           // offsets
-    b += align_up(sizeof(int32_t) * scan_ws_elems((int64_t)cells), 256);
-    b += 2 * align_up(sizeof(uint32_t) * (size_t)(n > 0 ? n : 1), 256);   // ping-pong keys/values
-    return b + 256;
+    return radix_table_bytes(n) + 2 * align_up(sizeof(uint32_t) * (size_t)(n > 0 ? n : 1), 256) + 256;   // ping-pong
 }
 
-// Sorts (keys, vals) by the low `bits` bits of the keys, stably.  The result
-// is left in (keys, vals); ws provides the ping-pong buffers.
-static spmv_status radix_sort_pairs(uint32_t *keys, int32_t *vals, int64_t n, int bits, void *ws, size_t ws_bytes,
-                                    hipStream_t s)
+// One pass over the 8 bits from `shift`; tws holds radix_table_bytes(n).
+template <typename V1, typename V2>
+static spmv_status radix_pass(const uint32_t *kin, const V1 *vin, const V2 *win, int64_t n, int shift, uint32_t *kout,
+                              V1 *vout, V2 *wout, void *tws, size_t tws_bytes, hipStream_t s)
 {
-    if (n <= 1 || bits <= 0) return SPMV_OK;
-    int64_t ntiles = ceil_div(n, RS_TILE);
-    size_t cells = (size_t)ntiles * RS_BINS;
-    WsCarver wc(ws, ws_bytes);
+    const int64_t ntiles = ceil_div(n, RS_TILE);
+    const size_t cells = radix_cells(n);
+    WsCarver wc(tws, tws_bytes);
     int32_t *counts = wc.take<int32_t>(cells);
     int32_t *offs = wc.take<int32_t>(cells + 1);
     int32_t *sws = wc.take<int32_t>(scan_ws_elems((int64_t)cells));
+    if (!wc.ok()) return fail(SPMV_ERR_INVALID_ARG, "radix sort: workspace too small");
+    radix_hist_kernel<<<(unsigned)ntiles, RS_THREADS, 0, s>>>(kin, n, shift, counts, ntiles);
+    SPMV_CHECK_LAUNCH("radix hist");
+    spmv_status st = exclusive_scan<int32_t, int32_t>(counts, (int64_t)cells, offs, sws, s);
+    if (st != SPMV_OK) return st;
+    radix_scatter_kernel<V1, V2><<<(unsigned)ntiles, RS_THREADS, 0, s>>>(kin, vin, win, n, shift, offs, ntiles, kout,
+                                                                         vout, wout);
+    SPMV_CHECK_LAUNCH("radix scatter");
+    return SPMV_OK;
+}
+
+__global__ void radix_init_kernel(const uint32_t *__restrict__ src, int64_t n, uint32_t *__restrict__ keys,
+                                  int32_t *__restrict__ vals);
+
+// Sorts by the low `bits` bits of the keys, stably; the result is left in
+// (keys, vals), ws provides the ping-pong buffers.  src == nullptr: sorts
+// (keys, vals) in place (an odd number of passes copies back at the end).
+// Otherwise the keys come from src, which stays as it is and is none of the
+// other arrays, and the values are the indices 0 .. n-1.
+static spmv_status radix_sort_pairs(uint32_t *keys, int32_t *vals, int64_t n, int bits, void *ws, size_t ws_bytes,
+                                    hipStream_t s, const uint32_t *src = nullptr)
+{
+    if (n <= 0) return SPMV_OK;
+    const int passes = n > 1 && bits > 0 ? (bits + 7) / 8 : 0;
+    if (passes == 0) {
+        if (src) {
+            radix_init_kernel<<<(unsigned)std::min<int64_t>(ceil_div(n, 256), 65536), 256, 0, s>>>(src, n, keys, vals);
+            SPMV_CHECK_LAUNCH("radix init");
+        }
+        return SPMV_OK;
+    }
+    WsCarver wc(ws, ws_bytes);
+    const size_t tb = radix_table_bytes(n);
+    void *tws = wc.take<char>(tb);
     uint32_t *k2 = wc.take<uint32_t>((size_t)n);
     int32_t *v2 = wc.take<int32_t>((size_t)n);
     if (!wc.ok()) return fail(SPMV_ERR_INVALID_ARG, "radix sort: workspace too small");
-    uint32_t *ka = keys, *kb = k2;
-    int32_t *va = vals, *vb = v2;
-    int passes = 0;
-    for (int shift = 0; shift < bits; shift += 8) {
-        radix_hist_kernel<<<(unsigned)ntiles, RS_THREADS, 0, s>>>(ka, n, shift, counts, ntiles);
-        SPMV_CHECK_LAUNCH("radix hist");
-        spmv_status st = exclusive_scan<int32_t, int32_t>(counts, (int64_t)cells, offs, sws, s);
+    const uint32_t *ka = src ? src : keys;
+    const int32_t *va = src ? nullptr : vals;
+    for (int p = 0; p < passes; ++p) {
+        // from src the last pass lands in (keys, vals); in place the first leaves them
+        const bool home = src ? ((passes - 1 - p) & 1) == 0 : (p & 1) != 0;
+        uint32_t *kb = home ? keys : k2;
+        int32_t *vb = home ? vals : v2;
+        spmv_status st = radix_pass<int32_t, NoPayload>(ka, va, nullptr, n, 8 * p, kb, vb, nullptr, tws, tb, s);
         if (st != SPMV_OK) return st;
-        radix_scatter_kernel<<<(unsigned)ntiles, RS_THREADS, 0, s>>>(ka, va, n, shift, offs, ntiles, kb, vb);
-        SPMV_CHECK_LAUNCH("radix scatter");
-        uint32_t *tk = ka; ka = kb; kb = tk;
-        int32_t *tv = va; va = vb; vb = tv;
-        ++passes;
+        ka = kb;
+        va = vb;
     }
-    if (passes & 1) {
+    if (ka != keys) {
         SPMV_HIP(hipMemcpyAsync(keys, ka, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, s));
         SPMV_HIP(hipMemcpyAsync(vals, va, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s));
     }
@@ -272,11 +401,14 @@ static unsigned grid_for(int64_t n)
     return (unsigned)(g < 1 ? 1 : g);
 }
 
-__global__ void iota_kernel(int32_t *out, int64_t n) { GRID_LOOP(i, n) out[i] = (int32_t)i; }
-
-__global__ void copy_u32_kernel(const int32_t *__restrict__ in, uint32_t *__restrict__ out, int64_t n)
+__global__ void radix_init_kernel(const uint32_t *__restrict__ src, int64_t n, uint32_t *__restrict__ keys,
+                                  int32_t *__restrict__ vals)
 {
-    GRID_LOOP(i, n) out[i] = (uint32_t)in[i];
+    GRID_LOOP(i, n)
+    {
+        keys[i] = src[i];
+        vals[i] = (int32_t)i;
+    }
 }
 
 __global__ void gather_u32_kernel(const int32_t *__restrict__ src, const int32_t *__restrict__ idx,
@@ -368,15 +500,23 @@ __global__ void validate_cols_kernel(const int32_t *__restrict__ col, int64_t nn
 __global__ void row_len_kernel(const int32_t *__restrict__ rp, int32_t n, int32_t *__restrict__ len,
                                int32_t *__restrict__ maxlen)
 {
+    __shared__ int32_t wmax[4];                  // blocks of 256
+    int32_t m = 0;
     GRID_LOOP(r, (int64_t)n)
     {
         int32_t l = rp[r + 1] - rp[r];
         len[r] = l;
-        atomicMax(maxlen, l);
+        m = max(m, l);
     }
+    // one atomic per workgroup: one per row serialised on the single counter
+    for (int off = WAVE / 2; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off, WAVE));
+    if (lane_id() == 0) wmax[threadIdx.x / WAVE] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicMax(maxlen, max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3])));
 }
 
-__global__ void desc_key_kernel(const int32_t *__restrict__ len, int32_t n, int32_t ndiag, uint32_t *__restrict__ key)
+// key may be len itself
+__global__ void desc_key_kernel(const int32_t *len, int32_t n, int32_t ndiag, uint32_t *key)
 {
     GRID_LOOP(r, (int64_t)n) key[r] = (uint32_t)(ndiag - len[r]);
 }
@@ -1129,10 +1269,8 @@ spmv_status spmv_csr_from_coo(int32_t n_rows, int32_t n_cols, int64_t nnz, const
     if (bad) return fail(SPMV_ERR_BAD_FORMAT, "spmv_csr_from_coo: row or column index out of range");
 
     // stable sort by column, then stably by row: order (row, col, input index)
-    copy_u32_kernel<<<grid_for(nnz), 256, 0, s>>>(col, keys, nnz);
-    iota_kernel<<<grid_for(nnz), 256, 0, s>>>(idx, nnz);
-    SPMV_CHECK_LAUNCH("coo init");
-    spmv_status st = radix_sort_pairs(keys, idx, nnz, bits_for(n_cols > 0 ? n_cols - 1 : 0), rws, rws_bytes, s);
+    spmv_status st = radix_sort_pairs(keys, idx, nnz, bits_for(n_cols > 0 ? n_cols - 1 : 0), rws, rws_bytes, s,
+                                      (const uint32_t *)col);
     if (st != SPMV_OK) return st;
     gather_u32_kernel<<<grid_for(nnz), 256, 0, s>>>(row, idx, keys, nnz);
     SPMV_CHECK_LAUNCH("coo gather rows");
@@ -1235,10 +1373,10 @@ spmv_status spmv_jds_from_csr(int32_t n, int64_t nnz, const int32_t *row_ptr, co
         return SPMV_OK;
     }
     // stable sort of the rows by decreasing length: key = ndiag - length
-    desc_key_kernel<<<grid_for(n), 256, 0, s>>>(len, n, ndiag, keys);
-    iota_kernel<<<grid_for(n), 256, 0, s>>>(perm, n);
+    uint32_t *skey = (uint32_t *)len;
+    desc_key_kernel<<<grid_for(n), 256, 0, s>>>(len, n, ndiag, skey);
     SPMV_CHECK_LAUNCH("jds keys");
-    spmv_status st = radix_sort_pairs(keys, perm, n, bits_for(ndiag), rws, rws_bytes, s);
+    spmv_status st = radix_sort_pairs(keys, perm, n, bits_for(ndiag), rws, rws_bytes, s, skey);
     if (st != SPMV_OK) return st;
     inverse_perm_kernel<<<grid_for(n), 256, 0, s>>>(perm, n, iperm);
     SPMV_CHECK_LAUNCH("jds iperm");
@@ -1447,10 +1585,10 @@ spmv_status spmv_jds_blocked_windowed_from_csr(int32_t n, int64_t nnz, const int
     if (read_flag(maxlen, &ndiag, s) != SPMV_OK) return SPMV_ERR_HIP;
     // rows by decreasing length (stable), then by window (stable): window-major,
     // longest first inside a window, ties in original order
-    desc_key_kernel<<<grid_for(n), 256, 0, s>>>(len, n, ndiag, keys);
-    iota_kernel<<<grid_for(n), 256, 0, s>>>(perm, n);
+    uint32_t *skey = (uint32_t *)len;
+    desc_key_kernel<<<grid_for(n), 256, 0, s>>>(len, n, ndiag, skey);
     SPMV_CHECK_LAUNCH("windowed keys");
-    spmv_status st = radix_sort_pairs(keys, perm, n, bits_for(ndiag), rws, rws_bytes, s);
+    spmv_status st = radix_sort_pairs(keys, perm, n, bits_for(ndiag), rws, rws_bytes, s, skey);
     if (st != SPMV_OK) return st;
     window_key_kernel<<<grid_for(n), 256, 0, s>>>(perm, n, sigma, keys);
     SPMV_CHECK_LAUNCH("windowed window keys");
@@ -1583,11 +1721,11 @@ spmv_status spmv_split_columns(int32_t n_rows, int32_t n_cols, int64_t nnz, cons
     if (n_rows > 0) SPMV_HIP(hipMemsetAsync(mask, 0, sizeof(uint32_t) * n_rows, s));
     if (nnz > 0) {
         row_of_entries_kernel<<<grid_for(nnz), 256, 0, s>>>(row_ptr, n_rows, nnz, rowid);
-        part_key_kernel<<<grid_for(nnz), 256, 0, s>>>(col_idx, nnz, width, keys);
-        iota_kernel<<<grid_for(nnz), 256, 0, s>>>(perm, nnz);
+        uint32_t *pkey = (uint32_t *)head;       // free until the head flags are written
+        part_key_kernel<<<grid_for(nnz), 256, 0, s>>>(col_idx, nnz, width, pkey);
         SPMV_CHECK_LAUNCH("split keys");
         // stable: each part keeps the row-major order of its entries
-        spmv_status st = radix_sort_pairs(keys, perm, nnz, bits_for(SPLIT_PARTS - 1), rws, rws_bytes, s);
+        spmv_status st = radix_sort_pairs(keys, perm, nnz, bits_for(SPLIT_PARTS - 1), rws, rws_bytes, s, pkey);
         if (st != SPMV_OK) return st;
         if (dt == SPMV_F64)
             gather_split_kernel<uint64_t><<<grid_for(nnz), 256, 0, s>>>(perm, nnz, col_idx, (const uint64_t *)val, rowid,
@@ -1898,10 +2036,8 @@ spmv_status spmv_transpose_csr(int32_t n_rows, int32_t n_cols, int64_t nnz, cons
     }
     // entries are in row order, so a stable sort by column lists each column's
     // entries by ascending row
-    copy_u32_kernel<<<grid_for(nnz), 256, 0, s>>>(col_idx, keys, nnz);
-    iota_kernel<<<grid_for(nnz), 256, 0, s>>>(tmap, nnz);
-    SPMV_CHECK_LAUNCH("transpose init");
-    spmv_status st = radix_sort_pairs(keys, tmap, nnz, bits_for(n_cols > 0 ? n_cols - 1 : 0), rws, rws_bytes, s);
+    spmv_status st = radix_sort_pairs(keys, tmap, nnz, bits_for(n_cols > 0 ? n_cols - 1 : 0), rws, rws_bytes, s,
+                                      (const uint32_t *)col_idx);
     if (st != SPMV_OK) return st;
     transpose_cols_kernel<<<grid_for(nnz), 256, 0, s>>>(row_ptr, n_rows, tmap, nnz, colT);
     ptr_from_sorted_kernel<uint32_t><<<grid_for((int64_t)n_cols + 1), 256, 0, s>>>(keys, nnz, n_cols, rowT_ptr);
