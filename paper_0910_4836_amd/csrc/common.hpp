@@ -44,6 +44,13 @@ spmv_status launch_combine(int32_t n, const int32_t *slot_ptr, const double *slo
 // 256 if the query fails.
 int device_cus();
 
+// Blocks of the CRS plans (crs.hip, plan.hip).
+constexpr int CRS_THREADS = 256;
+constexpr int CRS_MAX_BLOCK_NNZ = 4096;
+constexpr int CRS_MAX_BLOCK_ROWS = 256;          // rows of a block in general
+constexpr int CRS_MAX_SHORT_BLOCK_ROWS = 2048;   // rows of a block of short rows only
+constexpr int CRS_SHORT_ROW = 16;                // "short": at most this many entries
+
 // Default rows-block size of the CRS plans (crs.hip).
 int32_t crs_default_block_nnz();
 

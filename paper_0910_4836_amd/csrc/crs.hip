@@ -34,12 +34,7 @@
 
 namespace spmv {
 
-constexpr int CRS_THREADS = 256;
 constexpr int CRS_DEFAULT_BLOCK_NNZ = 1024;
-constexpr int CRS_MAX_BLOCK_NNZ = 4096;
-constexpr int CRS_MAX_BLOCK_ROWS = 256;          // rows of a block in general
-constexpr int CRS_MAX_SHORT_BLOCK_ROWS = 2048;   // rows of a block of short rows only
-constexpr int CRS_SHORT_ROW = 16;                // "short": at most this many entries
 constexpr int CRS_STREAM_U = 4;                  // stream mode: entries per lane per trip
 constexpr int CRS_LDS_ROUND = CRS_STREAM_U * CRS_THREADS;   // products per trip
 

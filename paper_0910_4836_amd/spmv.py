@@ -194,12 +194,19 @@ def spmv_csr_validate(A: CSR) -> bool:
 
 def spmv_crs_plan(A: CSR, block_nnz: int = 0) -> CSR:
     """Builds (and stores on A) the row-block plan used by spmv_crs / spmm_crs."""
+    lib = _lib.load()
     nb = C.c_int32(0)
-    st = _lib.load().spmv_crs_plan(A.n_rows, _p(A.row_ptr), block_nnz, None, 0, C.byref(nb), _stream())
-    if st not in (0, 3):
-        call("spmv_crs_plan", A.n_rows, _p(A.row_ptr), block_nnz, None, 0, C.byref(nb), _stream())
-    plan = torch.empty(nb.value + 1, dtype=_I32, device=A.device)
-    call("spmv_crs_plan", A.n_rows, _p(A.row_ptr), block_nnz, _p(plan), plan.numel(), C.byref(nb), _stream())
+    ws = _ws(lib.spmv_crs_plan_workspace_size(A.n_rows), A.device)
+    # a block and the row after it hold more than block_nnz entries, or the block has at least 256 rows
+    cap = 2 * -(-A.nnz // max(block_nnz or 1024, 1)) + A.n_rows // 256 + 2
+    args = lambda p: (A.n_rows, _p(A.row_ptr), block_nnz, _p(p), p.numel(), C.byref(nb), _p(ws), ws.numel(), _stream())
+    plan = torch.empty(cap, dtype=_I32, device=A.device)
+    st = lib.spmv_crs_plan_ws(*args(plan))
+    if st != 0:
+        if st == 3:                   # row_ptr and col_idx disagree on the entries
+            plan = torch.empty(nb.value + 1, dtype=_I32, device=A.device)
+        call("spmv_crs_plan_ws", *args(plan))
+    plan = plan[:nb.value + 1]
     A.plan, A.n_blocks, A.block_nnz = plan, nb.value, block_nnz
     return A
 

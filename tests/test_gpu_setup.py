@@ -40,3 +40,44 @@ def test_csr_from_coo_and_transpose_at_tile_edges(count, n_rows, n_cols):
     assert np.array_equal(to_np(tmap), order)
     assert np.array_equal(to_np(colT), np.repeat(np.arange(n_rows), np.diff(R.row_ptr))[order])
     assert np.array_equal(to_np(rowT), np.searchsorted(R.col[order], np.arange(n_cols + 1)))
+
+
+def host_plan(A, block_nnz):
+    """The plan of the host planner (spmv_crs_plan)."""
+    import ctypes as C
+    from paper_0910_4836_amd import _lib
+    nb = C.c_int32(0)
+    plan = torch.empty(2 * A.n_rows + 2, dtype=torch.int32, device="cuda")
+    _lib.call("spmv_crs_plan", A.n_rows, C.c_void_p(A.row_ptr.data_ptr()), block_nnz, C.c_void_p(plan.data_ptr()),
+              plan.numel(), C.byref(nb), None)
+    return to_np(plan)[:nb.value + 1]
+
+
+def csr_of_lengths(lengths):
+    rp = torch.from_numpy(np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)).cuda()
+    nnz = int(rp[-1])
+    return sp.CSR(len(lengths), 8, rp, torch.zeros(nnz, dtype=torch.int32, device="cuda"),
+                  torch.zeros(nnz, dtype=torch.float64, device="cuda"))
+
+
+@pytest.mark.parametrize("n", [1, 255, 257, 2047, 2049, 4095, 4096, 4097, 6144, 8193, 4096 * 33 + 17])
+@pytest.mark.parametrize("kind", ["empty", "short", "edge", "long", "mixed", "sparse"])
+def test_plan_on_the_gpu_is_the_host_plan(n, kind):
+    rng = np.random.default_rng(n)
+    lengths = {"empty": lambda: np.zeros(n, int), "short": lambda: rng.integers(0, 2, n),
+               "edge": lambda: rng.integers(14, 19, n), "long": lambda: rng.integers(200, 1200, n),
+               "mixed": lambda: np.where(rng.random(n) < 0.002, 5000, rng.integers(0, 40, n)),
+               "sparse": lambda: np.where(rng.random(n) < 0.0007, 17, 0)}[kind]()
+    A = csr_of_lengths(lengths)
+    for block_nnz in (0, 256, 1000, 4096):
+        sp.spmv_crs_plan(A, block_nnz)
+        assert np.array_equal(to_np(A.plan), host_plan(A, block_nnz)), block_nnz
+
+
+def test_plan_refuses_a_decreasing_row_ptr():
+    A = csr_of_lengths(np.full(9000, 3))
+    A.row_ptr[8000] += 4
+    with pytest.raises(sp.SpmvError, match="decreases"):
+        sp.spmv_crs_plan(A)
+    with pytest.raises(sp.SpmvError, match="block_nnz"):
+        sp.spmv_crs_plan(csr_of_lengths(np.full(10, 3)), 100)
