@@ -42,6 +42,48 @@ def test_csr_from_coo_and_transpose_at_tile_edges(count, n_rows, n_cols):
     assert np.array_equal(to_np(rowT), np.searchsorted(R.col[order], np.arange(n_cols + 1)))
 
 
+@pytest.mark.parametrize("n_rows,n_cols,count", [
+    (1, 1, 5000),                         # one key, summed in input order
+    (1, 9000, 2048), (1, 9000, 2049),     # small and large sort of one bucket
+    (1, 90_000, 8192), (1, 90_000, 8193), # the largest bucket, and one too many
+    (5000, 5000, 1024), (5000, 5000, 1025),
+    (70_000, 1000, 262_144), (70_000, 1000, 262_145),       # one radix pass, two
+    (400, 1 << 30, 30_000),               # 64-bit keys
+    (3_000_000, 40, 3000),                # mostly empty rows
+    (1_200_000, 3, 600_000)])
+@pytest.mark.parametrize("order", ["shuffled", "rows"])
+def test_csr_from_coo_buckets(n_rows, n_cols, count, order):
+    row, col, val = coo(count + n_rows, n_rows, n_cols, count)
+    if order == "rows":
+        by = np.argsort(row, kind="stable")
+        row, col, val = row[by], col[by], val[by]
+    check_csr(gpu_csr(sp, row, col, val, n_rows, n_cols), oracle.csr_from_coo(n_rows, n_cols, row, col, val))
+
+
+@pytest.mark.parametrize("heavy", [3000, 8192, 20_000])
+def test_csr_from_coo_one_heavy_row(heavy):
+    row, col, val = coo(heavy, 40_000, 50_000, 300_000)
+    row[::300_000 // heavy][:heavy] = 777
+    A = gpu_csr(sp, row, col, val, 40_000, 50_000)
+    check_csr(A, oracle.csr_from_coo(40_000, 50_000, row, col, val))
+    # values in 32 bits: no two of one position, so that nothing is summed
+    once = np.unique(row.astype(np.int64) * 50_000 + col, return_index=True)[1]
+    row, col, val = row[once], col[once], val[once]
+    by = np.random.default_rng(1).permutation(row.size)
+    F = gpu_csr(sp, row[by], col[by], val[by], 40_000, 50_000, torch.float32)
+    R = oracle.csr_from_coo(40_000, 50_000, row, col, val.astype(np.float32).astype(np.float64))
+    check_csr(F, R)
+
+
+@pytest.mark.parametrize("at", [0, 4999, 299_999])
+@pytest.mark.parametrize("bad", [(-1, 0), (40_000, 0), (0, -5), (0, 50_000)])
+def test_csr_from_coo_refuses_an_index_out_of_range(at, bad):
+    row, col, val = coo(2, 40_000, 50_000, 300_000)
+    row[at], col[at] = bad
+    with pytest.raises(sp.SpmvError, match="out of range"):
+        gpu_csr(sp, row, col, val, 40_000, 50_000)
+
+
 def host_plan(A, block_nnz):
     """The plan of the host planner (spmv_crs_plan)."""
     import ctypes as C
