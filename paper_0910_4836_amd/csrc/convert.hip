@@ -93,21 +93,233 @@ __device__ __forceinline__ int32_t row_of(const int32_t *__restrict__ rp, int32_
     return lo;
 }
 
-template <typename T>
-__global__ void jds_scatter_kernel(const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
-                                   const T *__restrict__ val, int32_t n, int64_t nnz, const int32_t *__restrict__ iperm,
-                                   const int32_t *__restrict__ jd_ptr, int symperm, int32_t *__restrict__ jd_col,
-                                   T *__restrict__ jd_val)
+// ---- CRS <-> JDS
+// Both directions transpose: a row's entries lie together in CRS, a
+// diagonal's in JDS.  Copied entry by entry one side of the copy is a 4- or
+// 8-byte access per 128-byte line.
+//   * Rows of more than 8 entries go through LDS in tiles of 64 permuted rows
+//     x 32 diagonals, both sides runs of consecutive addresses; a grid of
+//     fixed size walks the tiles.
+//   * Shorter rows are too small for runs on the CRS side, and in permuted
+//     order each of their lines would be fetched once per length that occurs
+//     in it.  They go one lane per row in the original order: the CRS side
+//     walks the arrays once, and as the sort is stable, rows of one length
+//     in a stretch of rows are neighbours on every diagonal.
+// Bound: the copy rate, and the partial lines at the ends of the runs.  30 M
+// entries, FP64 values, 2 M power-law rows (0.72 GB): CRS -> JDS 1375 -> 284
+// us, JDS -> CRS 1452 -> 312 us, of which the short rows take 66 (as tiles of
+// 256 rows x 8: 85-95).  Tiles of 128 or 256 rows, one range of tiles per XCD
+// and more workgroups all measure the same within 3%.
+constexpr int JT_THREADS = 256;
+constexpr int JT_ROWS = 64, JT_DIAGS = 32;          // a tile
+constexpr int JT_SHORT = 8;                         // rows of at most this many entries go by lanes
+constexpr int JT_STEPS = JT_ROWS * JT_DIAGS / JT_THREADS;
+constexpr int JT_PITCH = JT_DIAGS + 1;
+
+__device__ __forceinline__ int32_t diag_len(const int32_t *__restrict__ jp, int32_t d) { return jp[d + 1] - jp[d]; }
+
+// rows of more than JT_SHORT entries
+__device__ __forceinline__ int32_t jt_long_rows(const int32_t *__restrict__ jp, int32_t ndiag)
 {
-    GRID_LOOP(j, nnz)
-    {
-        const int32_t i = row_of(rp, n, j);
-        const int32_t d = (int32_t)(j - rp[i]);
-        const int64_t dst = (int64_t)jd_ptr[d] + iperm[i];
-        const int32_t c = col[j];
-        jd_col[dst] = symperm ? iperm[c] : c;
-        jd_val[dst] = val[j];
+    return ndiag > JT_SHORT ? diag_len(jp, JT_SHORT) : 0;
+}
+
+// Tiles of 32 diagonals in groups: group k covers 2^q tiles of each of the
+// row sets that reach its first diagonal, q as small as keeps the table of
+// group sizes in one workgroup (q = 0 up to 65,504 diagonals; a workgroup
+// that walks 4 to 16 tiles of one row set is 1-4% slower).
+constexpr int JT_GROUPS = SCAN_TILE;
+struct JtGroups {
+    int32_t K;                  // groups over the diagonals
+    int q;
+};
+
+static JtGroups jt_groups(int32_t ndiag)
+{
+    JtGroups g{1, 0};
+    while ((g.K = (int32_t)ceil_div(ndiag > 0 ? ndiag : 1, (int64_t)JT_DIAGS << g.q)) > JT_GROUPS - 1) ++g.q;
+    return g;
+}
+
+// prefix[k], k <= K: before group k.  C == 0: sets of JT_ROWS rows of more
+// than JT_SHORT entries; C > 0: tiles of BT_ROWS rows, whole slices of C rows.
+constexpr int BT_ROWS = 256;
+__global__ __launch_bounds__(SCAN_THREADS) void jt_table_kernel(const int32_t *__restrict__ jp, int32_t ndiag,
+                                                                int32_t C, JtGroups g,
+                                                                int32_t *__restrict__ prefix)
+{
+    __shared__ int32_t wt[SCAN_THREADS / WAVE];
+    const int32_t cut = jt_long_rows(jp, ndiag);
+    int32_t v[SCAN_ITEMS], sum = 0;
+#pragma unroll
+    for (int j = 0; j < SCAN_ITEMS; ++j) {
+        const int32_t k = (int32_t)threadIdx.x * SCAN_ITEMS + j;
+        v[j] = 0;
+        if (k < g.K) {
+            const int64_t reach = diag_len(jp, (k << g.q) * JT_DIAGS);
+            const int64_t sets = C == 0 ? (min((int64_t)cut, reach) + JT_ROWS - 1) / JT_ROWS
+                                        : ((reach + C - 1) / C * C + BT_ROWS - 1) / BT_ROWS;
+            v[j] = (int32_t)sets << (C == 0 ? 0 : g.q);
+        }
+        sum += v[j];
     }
+    int32_t total;
+    int32_t run = block_exclusive_scan<int32_t>(sum, wt, &total);
+#pragma unroll
+    for (int j = 0; j < SCAN_ITEMS; ++j) {
+        const int32_t k = (int32_t)threadIdx.x * SCAN_ITEMS + j;
+        if (k < g.K) prefix[k] = run;
+        run += v[j];
+    }
+    if (threadIdx.x == 0) prefix[g.K] = total;
+}
+
+// last k with prefix[k] <= b
+__device__ __forceinline__ int32_t jt_group(const int32_t *__restrict__ prefix, int32_t groups, int32_t b)
+{
+    int32_t lo = 0, hi = groups - 1;
+    while (lo < hi) {
+        const int32_t mid = (lo + hi + 1) >> 1;
+        if (prefix[mid] <= b) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+struct JtArgs {
+    const int32_t *rp;          // CRS row pointer
+    const int32_t *perm, *iperm;
+    const int32_t *jp;
+    int32_t n, ndiag;
+    JtGroups g;
+    const int32_t *prefix;      // K + 1 entries
+    int symperm;
+};
+
+template <bool TO_JDS, typename T>
+__global__ __launch_bounds__(JT_THREADS) void jds_transpose_kernel(JtArgs a, const int32_t *__restrict__ col_in,
+                                                                   const T *__restrict__ val_in,
+                                                                   int32_t *__restrict__ col_out,
+                                                                   T *__restrict__ val_out)
+{
+    __shared__ int32_t cs[JT_ROWS * JT_PITCH];
+    __shared__ T vs[JT_ROWS * JT_PITCH];
+    __shared__ int32_t at[JT_ROWS], len[JT_ROWS], jd[JT_DIAGS];
+    const int t = (int)threadIdx.x, lane = lane_id(), w = t / WAVE;
+    const int32_t sets = a.prefix[a.g.K], cut = jt_long_rows(a.jp, a.ndiag);
+    for (int32_t b = (int32_t)blockIdx.x; b < sets; b += (int32_t)gridDim.x) {
+        const int32_t k = jt_group(a.prefix, a.g.K, b);
+        const int32_t r0 = (b - a.prefix[k]) * JT_ROWS, nr = min(JT_ROWS, cut - r0);
+        const int64_t d_first = (int64_t)k * JT_DIAGS << a.g.q;
+        const int64_t d_end = min((int64_t)a.ndiag, d_first + (JT_DIAGS << a.g.q));
+        for (int64_t d0 = d_first; d0 < d_end; d0 += JT_DIAGS) {
+            __syncthreads();                                 // the tile before has been written
+            if (t < nr) {
+                const int32_t row = a.perm[r0 + t], s = a.rp[row];
+                at[t] = s + (int32_t)d0;
+                len[t] = min(a.rp[row + 1] - s - (int32_t)d0, JT_DIAGS);
+            }
+            if (t < JT_DIAGS) jd[t] = d0 + t < a.ndiag ? a.jp[d0 + t] + r0 : 0;
+            __syncthreads();
+            const int32_t depth = len[0];                    // rows by decreasing length
+            if (depth <= 0) break;
+            // side of the rows: 2^wlog lanes per row; side of the diagonals: a
+            // lane per row, a diagonal per wavefront
+            int wlog = 0;
+            while (1 << wlog < depth) ++wlog;
+            const int32_t step = JT_THREADS >> wlog, e = t & ((1 << wlog) - 1);
+            int32_t c[JT_STEPS];
+            T v[JT_STEPS];
+#pragma unroll
+            for (int j = 0; j < JT_STEPS; ++j) {
+                const int32_t i = TO_JDS ? (t >> wlog) + j * step : lane, d = TO_JDS ? e : w + j * (JT_THREADS / WAVE);
+                if (i < nr && d < len[i]) {
+                    const int64_t from = TO_JDS ? at[i] + d : jd[d] + i;
+                    c[j] = col_in[from];
+                    v[j] = val_in[from];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < JT_STEPS; ++j) {
+                const int32_t i = TO_JDS ? (t >> wlog) + j * step : lane, d = TO_JDS ? e : w + j * (JT_THREADS / WAVE);
+                if (i < nr && d < len[i]) {
+                    cs[i * JT_PITCH + d] = c[j];
+                    vs[i * JT_PITCH + d] = v[j];
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < JT_STEPS; ++j) {
+                const int32_t i = TO_JDS ? lane : (t >> wlog) + j * step, d = TO_JDS ? w + j * (JT_THREADS / WAVE) : e;
+                if (i < nr && d < len[i]) {
+                    const int64_t to = TO_JDS ? jd[d] + i : at[i] + d;
+                    const int32_t cc = cs[i * JT_PITCH + d];
+                    col_out[to] = !a.symperm ? cc : TO_JDS ? a.iperm[cc] : a.perm[cc];
+                    val_out[to] = vs[i * JT_PITCH + d];
+                }
+            }
+        }
+    }
+}
+
+template <bool TO_JDS, typename T>
+__global__ __launch_bounds__(JT_THREADS) void jds_short_rows_kernel(JtArgs a, const int32_t *__restrict__ col_in,
+                                                                    const T *__restrict__ val_in,
+                                                                    int32_t *__restrict__ col_out,
+                                                                    T *__restrict__ val_out)
+{
+    const int64_t row = xcd_remap(blockIdx.x, gridDim.x) * JT_THREADS + threadIdx.x;
+    if (row >= a.n) return;
+    const int32_t s = a.rp[row], len = a.rp[row + 1] - s, r = a.iperm[row];
+    if (len > JT_SHORT) return;
+    int32_t c[JT_SHORT];
+    T v[JT_SHORT];
+#pragma unroll
+    for (int d = 0; d < JT_SHORT; ++d)
+        if (d < len) {
+            const int64_t from = TO_JDS ? s + d : a.jp[d] + r;
+            c[d] = col_in[from];
+            v[d] = val_in[from];
+        }
+#pragma unroll
+    for (int d = 0; d < JT_SHORT; ++d)
+        if (d < len) {
+            const int64_t to = TO_JDS ? a.jp[d] + r : s + d;
+            col_out[to] = !a.symperm ? c[d] : TO_JDS ? a.iperm[c[d]] : a.perm[c[d]];
+            val_out[to] = v[d];
+        }
+}
+
+static size_t jt_ws_bytes() { return align_up(sizeof(int32_t) * (JT_GROUPS + 1), 256) + 256; }
+
+template <bool TO_JDS, typename T>
+static spmv_status jds_transpose(JtArgs a, const int32_t *col_in, const void *val_in, int32_t *col_out, void *val_out,
+                                 WsCarver &wc, hipStream_t s)
+{
+    a.g = jt_groups(a.ndiag);
+    int32_t *prefix = wc.take<int32_t>(JT_GROUPS + 1);
+    if (!wc.ok()) return fail(SPMV_ERR_INVALID_ARG, "CRS <-> JDS: workspace too small");
+    jt_table_kernel<<<1, SCAN_THREADS, 0, s>>>(a.jp, a.ndiag, 0, a.g, prefix);
+    SPMV_CHECK_LAUNCH("jds tiles");
+    a.prefix = prefix;
+    if (a.ndiag > JT_SHORT) {
+        jds_transpose_kernel<TO_JDS, T><<<(unsigned)(device_cus() * 5), JT_THREADS, 0, s>>>(
+            a, col_in, (const T *)val_in, col_out, (T *)val_out);
+        SPMV_CHECK_LAUNCH("jds transpose");
+    }
+    jds_short_rows_kernel<TO_JDS, T><<<(unsigned)ceil_div(a.n, JT_THREADS), JT_THREADS, 0, s>>>(
+        a, col_in, (const T *)val_in, col_out, (T *)val_out);
+    SPMV_CHECK_LAUNCH("jds short rows");
+    return SPMV_OK;
+}
+
+template <bool TO_JDS>
+static spmv_status jds_transpose_dt(spmv_dtype dt, const JtArgs &a, const int32_t *col_in, const void *val_in,
+                                    int32_t *col_out, void *val_out, WsCarver &wc, hipStream_t s)
+{
+    if (dt == SPMV_F64) return jds_transpose<TO_JDS, uint64_t>(a, col_in, val_in, col_out, val_out, wc, s);
+    if (dt == SPMV_BF16) return jds_transpose<TO_JDS, uint16_t>(a, col_in, val_in, col_out, val_out, wc, s);
+    return jds_transpose<TO_JDS, uint32_t>(a, col_in, val_in, col_out, val_out, wc, s);
 }
 
 // length of permuted row r from the diagonal lengths
@@ -128,36 +340,6 @@ __global__ void jds_row_len_kernel(const int32_t *__restrict__ jp, int32_t ndiag
     GRID_LOOP(r, (int64_t)n) len[perm[r]] = jds_len_of(jp, ndiag, r);
 }
 
-// diagonal holding JDS entry e: last d with jp[d] <= e
-__device__ __forceinline__ int32_t diag_of(const int32_t *__restrict__ jp, int32_t ndiag, int64_t e)
-{
-    int32_t lo = 0, hi = ndiag - 1;
-    while (lo < hi) {
-        int32_t mid = (lo + hi + 1) >> 1;
-        if ((int64_t)jp[mid] <= e) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
-template <typename T>
-__global__ void jds_to_csr_kernel(const int32_t *__restrict__ jp, int32_t ndiag, int64_t nnz,
-                                  const int32_t *__restrict__ perm, const int32_t *__restrict__ jd_col,
-                                  const T *__restrict__ jd_val, int symperm, const int32_t *__restrict__ rp,
-                                  int32_t *__restrict__ col, T *__restrict__ val)
-{
-    GRID_LOOP(e, nnz)
-    {
-        const int32_t d = diag_of(jp, ndiag, e);
-        const int32_t r = (int32_t)(e - jp[d]);
-        const int32_t i = perm[r];
-        const int64_t dst = (int64_t)rp[i] + d;
-        const int32_t c = jd_col[e];
-        col[dst] = symperm ? perm[c] : c;
-        val[dst] = jd_val[e];
-    }
-}
-
 __global__ void slice_nd_kernel(const int32_t *__restrict__ jp, int32_t ndiag, int32_t C, int32_t n_slices,
                                 int32_t *__restrict__ nd, int64_t *__restrict__ sz)
 {
@@ -169,30 +351,52 @@ __global__ void slice_nd_kernel(const int32_t *__restrict__ jp, int32_t ndiag, i
     }
 }
 
+// JDS -> blocked JDS: both sides lie along the rows.  A wavefront copies 64
+// rows of up to 32 diagonals, eight at a time; slots that their row does not
+// reach become padding.  Tiles of 256 rows x 32 diagonals.  Bound: the copy rate (449 ->
+// 142 us for 30 M entries with FP64 values).
+constexpr int BT_U = 8;
+
 template <typename T>
-__global__ void blocked_fill_kernel(const int32_t *__restrict__ jp, int32_t ndiag, const int32_t *__restrict__ jd_col,
-                                    const T *__restrict__ jd_val, int32_t n, int32_t C,
-                                    const int64_t *__restrict__ slice_ptr, int32_t n_slices, int64_t total,
-                                    int32_t *__restrict__ bl_col, T *__restrict__ bl_val)
+__global__ __launch_bounds__(BT_ROWS) void blocked_fill_kernel(const int32_t *__restrict__ jp, int32_t ndiag,
+                                                               const int32_t *__restrict__ jd_col,
+                                                               const T *__restrict__ jd_val, int32_t n_slices,
+                                                               int32_t C, const int64_t *__restrict__ slice_ptr,
+                                                               const int32_t *__restrict__ slice_nd, JtGroups g,
+                                                               const int32_t *__restrict__ prefix,
+                                                               int32_t *__restrict__ bl_col, T *__restrict__ bl_val)
 {
-    GRID_LOOP(k, total)
-    {
-        int32_t lo = 0, hi = n_slices - 1;
-        while (lo < hi) {
-            int32_t mid = (lo + hi + 1) >> 1;
-            if (slice_ptr[mid] <= k) lo = mid;
-            else hi = mid - 1;
-        }
-        const int64_t local = k - slice_ptr[lo];
-        const int32_t d = (int32_t)(local / C);
-        const int32_t rl = (int32_t)(local - (int64_t)d * C);
-        const int64_t r = (int64_t)lo * C + rl;
-        if (r < n && (int64_t)(jp[d + 1] - jp[d]) > r) {
-            bl_col[k] = jd_col[jp[d] + r];
-            bl_val[k] = jd_val[jp[d] + r];
-        } else {
-            bl_col[k] = -1;
-            bl_val[k] = T{};
+    const int32_t tiles = prefix[g.K];
+    for (int32_t b = (int32_t)blockIdx.x; b < tiles; b += (int32_t)gridDim.x) {
+        const int32_t k = jt_group(prefix, g.K, b), i0 = b - prefix[k];
+        const int64_t first = (((int64_t)k << g.q) + (i0 & ((1 << g.q) - 1))) * JT_DIAGS;
+        if (first >= ndiag) continue;
+        const int32_t d0 = (int32_t)first;
+        // C is a multiple of 64: a wavefront's rows are in one slice
+        const int64_t row0 = (int64_t)(i0 >> g.q) * BT_ROWS + (threadIdx.x & ~(WAVE - 1));
+        const int64_t sl = __builtin_amdgcn_readfirstlane((int)(row0 / C));
+        if (sl >= n_slices) continue;
+        const int32_t last = (int32_t)min((int64_t)slice_nd[sl], first + JT_DIAGS);
+        const int64_t r = row0 + lane_id(), dst0 = slice_ptr[sl] + (r - sl * C);
+        for (int32_t d = d0; d < last; d += BT_U) {
+            int32_t c[BT_U];
+            T v[BT_U];
+#pragma unroll
+            for (int u = 0; u < BT_U; ++u) {
+                const int32_t dd = min(d + u, ndiag - 1), from = jp[dd];
+                c[u] = -1;
+                v[u] = T{};
+                if (d + u < last && r < jp[dd + 1] - from) {
+                    c[u] = ld_stream(jd_col + from + r);
+                    v[u] = ld_stream(jd_val + from + r);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < BT_U; ++u)
+                if (d + u < last) {
+                    bl_col[dst0 + (int64_t)(d + u) * C] = c[u];
+                    bl_val[dst0 + (int64_t)(d + u) * C] = v[u];
+                }
         }
     }
 }
@@ -774,7 +978,7 @@ size_t spmv_jds_from_csr_workspace_size(int32_t n, int64_t nnz)
     b += align_up(sizeof(int32_t) * m, 256);        // lengths
     b += align_up(sizeof(uint32_t) * m, 256);       // keys
     b += align_up(sizeof(int32_t) * scan_ws_elems((int64_t)(m > (size_t)nnz ? m : (size_t)nnz)), 256);
-    b += radix_ws_bytes((int64_t)m);
+    b += radix_ws_bytes((int64_t)m) + jt_ws_bytes();
     return b + 1024;
 }
 
@@ -833,19 +1037,17 @@ spmv_status spmv_jds_from_csr(int32_t n, int64_t nnz, const int32_t *row_ptr, co
     } else {
         SPMV_HIP(hipMemsetAsync(jd_ptr, 0, sizeof(int32_t), s));
     }
-    const int sym = (flags & SPMV_SYMPERM) ? 1 : 0;
     if (nnz > 0) {
-        if (dt == SPMV_F64)
-            jds_scatter_kernel<uint64_t><<<grid_for(nnz), 256, 0, s>>>(row_ptr, col_idx, (const uint64_t *)val, n, nnz,
-                                                                     iperm, jd_ptr, sym, jd_col, (uint64_t *)jd_val);
-        else if (dt == SPMV_F32 || dt == SPMV_I32)
-            jds_scatter_kernel<uint32_t><<<grid_for(nnz), 256, 0, s>>>(row_ptr, col_idx, (const uint32_t *)val, n, nnz,
-                                                                    iperm, jd_ptr, sym, jd_col, (uint32_t *)jd_val);
-        else
-            jds_scatter_kernel<uint16_t><<<grid_for(nnz), 256, 0, s>>>(row_ptr, col_idx, (const uint16_t *)val, n,
-                                                                       nnz, iperm, jd_ptr, sym, jd_col,
-                                                                       (uint16_t *)jd_val);
-        SPMV_CHECK_LAUNCH("jds scatter");
+        JtArgs t{};
+        t.rp = row_ptr;
+        t.perm = perm;
+        t.iperm = iperm;
+        t.jp = jd_ptr;
+        t.n = n;
+        t.ndiag = ndiag;
+        t.symperm = (flags & SPMV_SYMPERM) ? 1 : 0;
+        st = jds_transpose_dt<true>(dt, t, col_idx, val, jd_col, jd_val, wc, s);
+        if (st != SPMV_OK) return st;
     }
     if (h_jd_ptr)
         SPMV_HIP(hipMemcpyAsync(h_jd_ptr, jd_ptr, sizeof(int32_t) * ((size_t)ndiag + 1), hipMemcpyDeviceToHost, s));
@@ -856,7 +1058,8 @@ spmv_status spmv_jds_from_csr(int32_t n, int64_t nnz, const int32_t *row_ptr, co
 size_t spmv_jds_to_csr_workspace_size(int32_t n)
 {
     size_t m = (size_t)(n > 0 ? n : 1);
-    return align_up(sizeof(int32_t) * m, 256) + align_up(sizeof(int32_t) * scan_ws_elems((int64_t)m), 256) + 512;
+    return align_up(sizeof(int32_t) * m, 256) + align_up(sizeof(int32_t) * scan_ws_elems((int64_t)m), 256) +
+           jt_ws_bytes() + 512;
 }
 
 spmv_status spmv_jds_to_csr(int32_t n, const int32_t *perm, const int32_t *jd_ptr, int32_t ndiag, const int32_t *jd_col,
@@ -881,24 +1084,25 @@ spmv_status spmv_jds_to_csr(int32_t n, const int32_t *perm, const int32_t *jd_pt
     SPMV_CHECK_LAUNCH("jds_to_csr lengths");
     spmv_status st = exclusive_scan<int32_t, int32_t>(len, n, row_ptr, sws, s);
     if (st != SPMV_OK) return st;
-    int32_t nnz = 0;
-    SPMV_HIP(hipMemcpyAsync(&nnz, row_ptr + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    SPMV_HIP(hipStreamSynchronize(s));
-    if (nnz == 0) return SPMV_OK;
-    SPMV_REQUIRE(jd_col && jd_val && col_idx && val, "spmv_jds_to_csr: null arrays");
-    const int sym = (flags & SPMV_SYMPERM) ? 1 : 0;
-    if (dt == SPMV_F64)
-        jds_to_csr_kernel<uint64_t><<<grid_for(nnz), 256, 0, s>>>(jd_ptr, ndiag, nnz, perm, jd_col,
-                                                                (const uint64_t *)jd_val, sym, row_ptr, col_idx,
-                                                                (uint64_t *)val);
-    else if (dt == SPMV_F32 || dt == SPMV_I32)
-        jds_to_csr_kernel<uint32_t><<<grid_for(nnz), 256, 0, s>>>(jd_ptr, ndiag, nnz, perm, jd_col, (const uint32_t *)jd_val,
-                                                               sym, row_ptr, col_idx, (uint32_t *)val);
-    else
-        jds_to_csr_kernel<uint16_t><<<grid_for(nnz), 256, 0, s>>>(jd_ptr, ndiag, nnz, perm, jd_col,
-                                                                  (const uint16_t *)jd_val, sym, row_ptr, col_idx,
-                                                                  (uint16_t *)val);
-    SPMV_CHECK_LAUNCH("jds_to_csr scatter");
+    if (ndiag == 0) return SPMV_OK;
+    if (!(jd_col && jd_val && col_idx && val)) {         // only a matrix without entries needs no arrays
+        int32_t nnz = 0;
+        if (read_flag(row_ptr + n, &nnz, s) != SPMV_OK) return SPMV_ERR_HIP;
+        SPMV_REQUIRE(nnz == 0, "spmv_jds_to_csr: null arrays");
+        return SPMV_OK;
+    }
+    JtArgs t{};
+    t.rp = row_ptr;
+    t.perm = perm;
+    t.iperm = len;                                       // the lengths are in row_ptr now
+    inverse_perm_kernel<<<grid_for(n), 256, 0, s>>>(perm, n, len);
+    SPMV_CHECK_LAUNCH("jds_to_csr iperm");
+    t.jp = jd_ptr;
+    t.n = n;
+    t.ndiag = ndiag;
+    t.symperm = (flags & SPMV_SYMPERM) ? 1 : 0;
+    st = jds_transpose_dt<false>(dt, t, jd_col, jd_val, col_idx, val, wc, s);
+    if (st != SPMV_OK) return st;
     return SPMV_OK;
 }
 
@@ -920,7 +1124,7 @@ size_t spmv_jds_blocked_workspace_size(int32_t n, int32_t ndiag, int32_t C, unsi
     size_t ns = (size_t)ceil_div(n > 0 ? n : 1, C);
     size_t b = align_up(sizeof(int64_t) * ns, 256) + align_up(sizeof(int64_t) * scan_ws_elems((int64_t)ns), 256);
     if (flags & SPMV_SOJDS) b += align_up(sizeof(uint32_t) * ns * (size_t)ceil_div(ndiag > 0 ? ndiag : 1, 32), 256);
-    return b + 1024;
+    return b + jt_ws_bytes() + 1024;
 }
 
 spmv_status spmv_jds_blocked_from_jds(int32_t n, const int32_t *jd_ptr, int32_t ndiag, const int32_t *jd_col,
@@ -943,6 +1147,7 @@ spmv_status spmv_jds_blocked_from_jds(int32_t n, const int32_t *jd_ptr, int32_t 
     uint32_t *taken = (flags & SPMV_SOJDS) ? wc.take<uint32_t>((size_t)(ns > 0 ? ns : 1) *
                                                                (size_t)ceil_div(ndiag > 0 ? ndiag : 1, 32))
                                            : nullptr;
+    int32_t *prefix = wc.take<int32_t>(JT_GROUPS + 1);
     if (ns == 0) {
         SPMV_HIP(hipMemsetAsync(slice_ptr, 0, sizeof(int64_t), s));
         SPMV_HIP(hipStreamSynchronize(s));
@@ -963,10 +1168,13 @@ spmv_status spmv_jds_blocked_from_jds(int32_t n, const int32_t *jd_ptr, int32_t 
     if (total == 0) return SPMV_OK;
     SPMV_REQUIRE(jd_col && jd_val && bl_col && bl_val, "spmv_jds_blocked_from_jds: null arrays");
     const int32_t words = (int32_t)ceil_div(ndiag > 0 ? ndiag : 1, 32);
+    const JtGroups g = jt_groups(ndiag);
+    jt_table_kernel<<<1, SCAN_THREADS, 0, s>>>(jd_ptr, ndiag, C, g, prefix);
+    SPMV_CHECK_LAUNCH("blocked tiles");
 #define BLK_CASE(DT, T)                                                                                             \
     if (dt == DT) {                                                                                                 \
-        blocked_fill_kernel<T><<<grid_for(total), 256, 0, s>>>(jd_ptr, ndiag, jd_col, (const T *)jd_val, n, C,      \
-                                                               slice_ptr, ns, total, bl_col, (T *)bl_val);          \
+        blocked_fill_kernel<T><<<(unsigned)(device_cus() * 8), BT_ROWS, 0, s>>>(                                    \
+            jd_ptr, ndiag, jd_col, (const T *)jd_val, ns, C, slice_ptr, slice_nd, g, prefix, bl_col, (T *)bl_val);  \
         SPMV_CHECK_LAUNCH("blocked fill");                                                                          \
         if (flags & SPMV_SOJDS) {                                                                                   \
             sojds_wave_kernel<T><<<(unsigned)ns, WAVE, 0, s>>>(jd_ptr, ndiag, jd_col, (const T *)jd_val, n, C,       \

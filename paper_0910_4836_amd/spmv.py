@@ -226,12 +226,18 @@ def jds_from_csr(A: CSR, symperm: bool = False) -> JDS:
     args = lambda cap, jp, hjp: (n, nnz, _p(A.row_ptr), _p(A.col_idx), _p(A.val), dtype_code(A.val.dtype), flags,
                                  _p(perm), _p(iperm), jp, cap, _p(jd_col), _p(jd_val), C.byref(nd), hjp, _p(ws),
                                  ws.numel(), _stream())
-    st = lib.spmv_jds_from_csr(*args(0, None, None))
-    if st not in (0, 3):
-        call("spmv_jds_from_csr", *args(0, None, None))
-    jd_ptr = torch.empty(nd.value + 1, dtype=_I32, device=dev)
-    h_jd_ptr = np.zeros(nd.value + 1, dtype=np.int32)
-    call("spmv_jds_from_csr", *args(nd.value + 1, _p(jd_ptr), _h_i32(h_jd_ptr)))
+    # room for 4,096 diagonals saves most matrices the call that only counts them
+    cap = min(A.n_cols, 4096) + 1
+    while True:
+        jd_ptr = torch.empty(cap, dtype=_I32, device=dev)
+        h_jd_ptr = np.zeros(cap, dtype=np.int32)
+        st = lib.spmv_jds_from_csr(*args(cap, _p(jd_ptr), _h_i32(h_jd_ptr)))
+        if st == 0:
+            break
+        if st != 3 or cap == nd.value + 1:
+            call("spmv_jds_from_csr", *args(cap, _p(jd_ptr), _h_i32(h_jd_ptr)))
+        cap = nd.value + 1
+    jd_ptr, h_jd_ptr = jd_ptr[:nd.value + 1], h_jd_ptr[:nd.value + 1].copy()
     return JDS(n, A.n_cols, perm[:n], iperm[:n], jd_ptr, h_jd_ptr, jd_col[:nnz], jd_val[:nnz], symperm)
 
 
@@ -258,17 +264,14 @@ def jds_blocked_from_jds(J: JDS, C_: int = 64, sojds: bool = False) -> Blocked:
     slice_nd = torch.empty(max(ns, 1), dtype=_I32, device=dev)
     h_slice_nd = np.zeros(max(ns, 1), dtype=np.int32)
     padded = C.c_int64(0)
-    args = lambda cap, bc, bv: (J.n, _p(J.jd_ptr), J.ndiag, _p(J.jd_col), _p(J.jd_val), dtype_code(J.jd_val.dtype),
-                                C_, flags, _p(slice_ptr), _p(slice_nd), bc, bv, cap, C.byref(padded),
-                                _h_i32(h_slice_nd), _p(ws), ws.numel(), _stream())
-    st = lib.spmv_jds_blocked_from_jds(*args(0, None, None))
-    if st not in (0, 3):
-        call("spmv_jds_blocked_from_jds", *args(0, None, None))
-    tot = padded.value
+    # diagonal d lies in the slices whose first row it reaches
+    tot = int(-(-np.diff(J.h_jd_ptr.astype(np.int64)) // max(C_, 1)).sum()) * C_
     bl_col = torch.empty(max(tot, 1), dtype=_I32, device=dev)
     bl_val = torch.empty(max(tot, 1), dtype=J.jd_val.dtype, device=dev)
-    if tot > 0:
-        call("spmv_jds_blocked_from_jds", *args(tot, _p(bl_col), _p(bl_val)))
+    call("spmv_jds_blocked_from_jds", J.n, _p(J.jd_ptr), J.ndiag, _p(J.jd_col), _p(J.jd_val),
+         dtype_code(J.jd_val.dtype), C_, flags, _p(slice_ptr), _p(slice_nd), _p(bl_col), _p(bl_val), max(tot, 1),
+         C.byref(padded), _h_i32(h_slice_nd), _p(ws), ws.numel(), _stream())
+    tot = padded.value
     return Blocked(J.n, J.n_cols, C_, J.perm, slice_ptr, slice_nd[:ns], h_slice_nd[:ns].copy(), bl_col[:tot],
                    bl_val[:tot], tot, J.symperm, sojds)
 

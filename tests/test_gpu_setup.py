@@ -123,3 +123,48 @@ def test_plan_refuses_a_decreasing_row_ptr():
         sp.spmv_crs_plan(A)
     with pytest.raises(sp.SpmvError, match="block_nnz"):
         sp.spmv_crs_plan(csr_of_lengths(np.full(10, 3)), 100)
+
+
+def csr_of_rows(lengths, n_cols, seed):
+    """CRS whose row i has lengths[i] entries in distinct ascending columns (an arithmetic run of them)."""
+    rng = np.random.default_rng(seed)
+    rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    at = np.arange(rp[-1]) - np.repeat(rp[:-1], lengths)
+    step = np.repeat(np.maximum(n_cols // np.maximum(lengths, 1), 1), lengths)
+    col = (at * step + np.repeat(rng.integers(0, 2, len(lengths)), lengths) * (step > 1)).astype(np.int32)
+    return rp, col, rng.standard_normal(rp[-1])
+
+
+SHAPES = {
+    "one row": lambda rng: np.array([7]),
+    "short": lambda rng: rng.integers(0, 9, 3000),
+    "edge of short": lambda rng: rng.integers(7, 11, 1000),
+    "tile edges": lambda rng: np.repeat([31, 32, 33, 63, 64, 65], [65, 64, 63, 1, 2, 129]),
+    "long": lambda rng: np.concatenate([[5000, 4097, 300], rng.integers(0, 50, 700)]),
+    "empty rows": lambda rng: np.where(rng.random(2000) < 0.7, 0, rng.integers(0, 20, 2000)),
+    "more than 65504 diagonals": lambda rng: np.concatenate([[70_000], rng.integers(0, 12, 300)]),
+}
+
+
+@pytest.mark.parametrize("shape", list(SHAPES))
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32, torch.bfloat16, torch.int32])
+def test_jds_and_blocked_at_tile_edges(shape, dtype):
+    lengths = SHAPES[shape](np.random.default_rng(11))
+    n_cols = max(int(lengths.max()), len(lengths))
+    rp, col, val = csr_of_rows(lengths, n_cols, 3)
+    val = torch.from_numpy(val * 100).to(dtype)
+    R = oracle.CSR(len(lengths), n_cols, rp, col, val.double().numpy())
+    A = sp.CSR(len(lengths), n_cols, torch.from_numpy(rp).cuda(), torch.from_numpy(col).cuda(), val.cuda())
+    J, RJ = sp.jds_from_csr(A), oracle.jds_from_csr(R)
+    for got, want in ((J.perm, RJ.perm), (J.iperm, RJ.iperm), (J.jd_ptr, RJ.jd_ptr), (J.jd_col, RJ.jd_col),
+                      (J.jd_val.double(), RJ.jd_val)):
+        assert np.array_equal(to_np(got), want)
+    assert np.array_equal(J.h_jd_ptr, RJ.jd_ptr)
+    B = sp.jds_to_csr(J)
+    for got, want in ((B.row_ptr, rp), (B.col_idx, col), (B.val.double(), R.val)):
+        assert np.array_equal(to_np(got), want)
+    for C_ in (64, 192):
+        K, RK = sp.jds_blocked_from_jds(J, C_), oracle.blocked_from_jds(RJ, C_)
+        assert np.array_equal(to_np(K.slice_ptr), RK.slice_ptr)
+        assert np.array_equal(to_np(K.bl_col), RK.bl_col)
+        assert np.array_equal(to_np(K.bl_val.double()), RK.bl_val)
