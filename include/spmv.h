@@ -454,6 +454,23 @@ spmv_status spmv_grad_vals_jds(int32_t n, const int32_t *perm, const int32_t *jd
                                const int32_t *jd_col, const void *g, const void *x, void *dval,
                                spmv_dtype dt, double alpha, double beta, unsigned flags, void *stream);
 
+/* Several value gradients summed in one pass over the entries:
+ * dval = sum_j alpha_j * g_j[row] * x_j[col] + beta * dval, 1 <= m <=
+ * SPMV_GRAD_MAX_PAIRS pairs (h_g, h_x: host arrays of m device pointers,
+ * h_alpha: m factors), added in order and rounded to dt after each, i.e. bit
+ * for bit the m calls of spmv_grad_vals_jds with beta, then 1.  dval must not
+ * overlap the vectors.  tiles, n_tiles, h_plan: a plan of spmv_jds_tiles for
+ * the matrix.  ws: spmv_grad_vals_jds_sum_workspace_size(n_cols, m, dt),
+ * 16-byte aligned (the x_j side by side).  Asynchronous. */
+#define SPMV_GRAD_MAX_PAIRS 8
+size_t spmv_grad_vals_jds_sum_workspace_size(int32_t n_cols, int32_t m, spmv_dtype dt);
+spmv_status spmv_grad_vals_jds_sum(int32_t n, int32_t n_cols, const int32_t *perm, const int32_t *jd_ptr,
+                                   int32_t ndiag, const int32_t *jd_col, int32_t m,
+                                   const void *const *h_g, const void *const *h_x, const double *h_alpha,
+                                   void *dval, spmv_dtype dt, double beta, const int32_t *tiles,
+                                   int64_t n_tiles, const int64_t *h_plan, unsigned flags, void *ws,
+                                   size_t ws_bytes, void *stream);
+
 /* ======================================================================== */
 /* Column-split products                                                     */
 /* ======================================================================== */

@@ -17,6 +17,7 @@ WIDE_ROW_NNZ = 4096
 BATCHED_PLAN_WORDS = 12
 SPLIT_PARTS = 8
 DIA_MAX = 64           # SPMV_DIA_MAX
+GRAD_MAX_PAIRS = 8     # SPMV_GRAD_MAX_PAIRS
 
 STATUS = {0: "ok", 1: "invalid argument", 2: "bad matrix format", 3: "output capacity too small",
           4: "unsupported", 5: "HIP runtime error"}
@@ -86,6 +87,9 @@ SIGNATURES = {
     "spmm_jds_blocked": (_int, [_i32, _i32, _p, _i32, _i32, _p, _p, _p, _p, _int, _i32, _p, _i64, _p, _i64, _int,
                                 _f64, _f64, _p, _i32, _p, _sz, _p]),
     "spmv_grad_vals_jds": (_int, [_i32, _p, _p, _i32p, _i32, _i64, _p, _p, _p, _p, _int, _f64, _f64, _u32, _p]),
+    "spmv_grad_vals_jds_sum_workspace_size": (_sz, [_i32, _i32, _int]),
+    "spmv_grad_vals_jds_sum": (_int, [_i32, _i32, _p, _p, _i32, _p, _i32, _vpp, _vpp, C.POINTER(_f64), _p, _int, _f64,
+                                      _p, _i64, _i64p, _u32, _p, _sz, _p]),
     "spmv_split_columns_workspace_size": (_sz, [_i32, _i64]),
     "spmv_split_columns": (_int, [_i32, _i32, _i64, _p, _p, _p, _int, _i32, _p, _p, _p, _p, _p, _i64p, _i64p, _p, _sz,
                                   _p]),

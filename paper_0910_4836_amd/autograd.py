@@ -25,6 +25,7 @@ import numpy as np
 import torch
 
 from . import spmv as S
+from ._lib import GRAD_MAX_PAIRS
 
 
 class SpMVOperator:
@@ -92,6 +93,20 @@ class SpMVOperator:
 
     def grad_vals(self, g, x, out=None, alpha=1.0, beta=0.0):
         return S.spmv_grad_vals_jds(self.J, g, x, out, alpha, beta)
+
+    def grad_vals_sum(self, pairs, out, beta=0.0):
+        """out = sum alpha*g[row]*x[col] (+ beta*out) over pairs (alpha, g, x), in order."""
+        if self.nnz == 0:
+            return out
+        for i in range(0, len(pairs), GRAD_MAX_PAIRS):
+            some = pairs[i:i + GRAD_MAX_PAIRS]
+            if len(some) == 1:
+                alpha, g, x = some[0]
+                self.grad_vals(g, x, out, alpha=alpha, beta=beta)
+            else:
+                S.spmv_grad_vals_jds_sum(self.J, some, out, beta)
+            beta = 1.0
+        return out
 
 
 class SpMVFunction(torch.autograd.Function):
@@ -182,17 +197,23 @@ class ChebyshevLoss(torch.autograd.Function):
                 lo = s
             for k in range(lo, e - 1):
                 ys[k + 1] = _step(op, vals, ys[k], ys[k - 1])
-            # reverse sweep over steps k = e-1 .. max(s, 1) (step k makes y_{k+1})
+            # reverse sweep over steps k = e-1 .. max(s, 1) (step k makes y_{k+1});
+            # the segment's value gradients are summed in one pass at its end
+            pairs = []
             for k in range(min(e, K) - 1, max(s, 1) - 1, -1):
                 bk1 = bar.pop(k + 1)
                 op.rmatvec(vals, bk1, get_bar(k), alpha=2.0, beta=1.0)
                 S.spmv_axpby(-1.0, bk1, 1.0, get_bar(k - 1))
-                op.grad_vals(bk1, ys[k], dvals, alpha=2.0, beta=0.0 if first_dval else 1.0)
-                first_dval = False
+                pairs.append((2.0, bk1, ys[k]))
+                if len(pairs) == GRAD_MAX_PAIRS:
+                    op.grad_vals_sum(pairs, dvals, beta=0.0 if first_dval else 1.0)
+                    first_dval, pairs = False, []
             if s == 0:
                 b1 = bar.pop(1)
                 op.rmatvec(vals, b1, get_bar(0), alpha=1.0, beta=1.0)
-                op.grad_vals(b1, x, dvals, alpha=1.0, beta=0.0 if first_dval else 1.0)
+                pairs.append((1.0, b1, x))
+            if pairs:
+                op.grad_vals_sum(pairs, dvals, beta=0.0 if first_dval else 1.0)
                 first_dval = False
         dx = bar.pop(0)
         return dvals, dx, None, None, None

@@ -533,6 +533,116 @@ __global__ __launch_bounds__(JDS_THREADS) void jds_grad_kernel(JdsArgs a, JdsPla
     else jds_grad_lane<false, U, T>(a, t);
 }
 
+// Sum of several value gradients in one pass: dval[e] = sum_j (alpha_j *
+// g_j[row]) * x_j[col[e]] (+ beta*dval[e]), j in order, each term in FP64 and
+// the sum rounded to T after each term, so that it equals m calls of the
+// single gradient bit for bit.  The m vectors x_j are staged as rows of M (the
+// power of two >= m) consecutive elements first: an entry then gathers one
+// row, at most 64 bytes of one line, instead of m lines, and its column is
+// read and its gradient written once.  Launched from the XCD-local tile plan:
+// the staged rows are M times as large as x, and each XCD's part of a band
+// stays in its own L2 only if its rows are neighbours.
+// 80 M entries, FP32, five pairs (one checkpoint segment of the recurrence):
+// five single calls 2010 us, one call 765 us (36 of them staging).
+constexpr int GRAD_PAIRS = SPMV_GRAD_MAX_PAIRS;
+
+struct GradPairs {
+    const void *g[GRAD_PAIRS];
+    const void *x[GRAD_PAIRS];
+    double alpha[GRAD_PAIRS];
+    int m;
+};
+
+template <int M, typename T>
+struct alignas(M * sizeof(T) < 16 ? M * sizeof(T) : 16) GradRow {
+    T v[M];
+};
+
+template <int M, typename T>
+__global__ __launch_bounds__(256) void grad_stage_kernel(GradPairs p, int64_t n, GradRow<M, T> *__restrict__ out)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    GradRow<M, T> r;
+#pragma unroll
+    for (int j = 0; j < M; ++j) r.v[j] = j < p.m ? ((const T *)p.x[j])[i] : T(0);
+    out[i] = r;
+}
+
+template <bool UNI, int U, int M, typename T>
+__device__ __forceinline__ void jds_grad_rows_lane(const JdsArgs &a, const WaveTask &t, const GradPairs &p,
+                                                   const GradRow<M, T> *__restrict__ X)
+{
+#pragma clang fp contract(off)
+    const int32_t *__restrict__ jp = a.jd_ptr;
+    const int32_t *__restrict__ col = a.col;
+    T *__restrict__ dval = (T *)a.dval;
+    const int32_t row = a.symperm ? t.r : a.perm[t.r];
+    double gv[M];
+#pragma unroll
+    for (int j = 0; j < M; ++j) gv[j] = j < p.m ? p.alpha[j] * to_f64(((const T *)p.g[j])[row]) : 0.0;
+    int32_t dA = t.dA, dB = t.dB, row0 = t.row0, kk = t.kk, G = t.G;
+    if (UNI) {                                 // see jds_diag_sum
+        dA = __builtin_amdgcn_readfirstlane(dA);
+        dB = __builtin_amdgcn_readfirstlane(dB);
+        row0 = __builtin_amdgcn_readfirstlane(row0);
+        kk = 0;
+        G = 1;
+    }
+    for (int32_t base = dA; base < dB; base += G * U) {
+        if (!t.bounded && jp[base + 1] - jp[base] <= row0) break;
+        int32_t off[U], len[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            int32_t dd = base + kk + u * G;
+            dd = dd < dB ? dd : dB - 1;
+            off[u] = jp[dd];
+            len[u] = jp[dd + 1] - off[u];
+        }
+        int32_t c[U];
+        T old[U];
+        bool act[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            act[u] = base + kk + u * G < dB && t.r < len[u];
+            if (act[u]) {
+                c[u] = ld_stream(col + off[u] + t.r);
+                if (a.beta != 0.0) old[u] = dval[(int64_t)off[u] + t.r];
+            }
+        }
+        GradRow<M, T> xr[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (act[u]) xr[u] = X[c[u]];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (!act[u]) continue;
+            double v = gv[0] * to_f64(xr[u].v[0]);
+            if (a.beta != 0.0) v = fma(a.beta, to_f64(old[u]), v);
+            T r = (T)v;
+#pragma unroll
+            for (int j = 1; j < M; ++j)
+                if (j < p.m) r = (T)(to_f64(r) + gv[j] * to_f64(xr[u].v[j]));
+            dval[(int64_t)off[u] + t.r] = r;
+        }
+    }
+}
+
+template <int U, int M, typename T>
+__global__ __launch_bounds__(JDS_THREADS) void jds_grad_rows_kernel(JdsArgs a, const int32_t *__restrict__ tiles,
+                                                                    TileBounds xb, GradPairs p,
+                                                                    const GradRow<M, T> *__restrict__ X)
+{
+    const int x = (int)(blockIdx.x % 8);
+    const int64_t idx = xb.b[x] + blockIdx.x / 8;
+    if (idx >= xb.b[x + 1]) return;
+    const int32_t row0 = tiles[2 * idx], code = tiles[2 * idx + 1];
+    const WaveTask t = tile_task<FMT_JDS>(a, row0, code >> 8, code & 15, (code >> 4) & 15, false);
+    if (!t.row_ok) return;
+    if (t.G == 1) jds_grad_rows_lane<true, U, M, T>(a, t, p, X);
+    else jds_grad_rows_lane<false, U, M, T>(a, t, p, X);
+}
+
 // ---------------------------------------------------------------- host planning
 
 // W wavefronts per 64-row chunk, split into (R rows per wave, S waves per
@@ -1248,6 +1358,82 @@ spmv_status spmv_grad_vals_jds(int32_t n, const int32_t *perm, const int32_t *jd
     else
         jds_grad_kernel<4, float><<<grid, P.waves * WAVE, 0, s>>>(a, P);
     SPMV_CHECK_LAUNCH("spmv_grad_vals_jds");
+    return SPMV_OK;
+}
+
+static int grad_row_elems(int32_t m)
+{
+    int M = 2;
+    while (M < m) M <<= 1;
+    return M;
+}
+
+size_t spmv_grad_vals_jds_sum_workspace_size(int32_t n_cols, int32_t m, spmv_dtype dt)
+{
+    if (n_cols <= 0 || m < 1 || m > GRAD_PAIRS || !valid_vec_dtype(dt)) return 256;
+    return align_up((size_t)n_cols * grad_row_elems(m) * dtype_size(dt), 256) + 256;
+}
+
+spmv_status spmv_grad_vals_jds_sum(int32_t n, int32_t n_cols, const int32_t *perm, const int32_t *jd_ptr,
+                                   int32_t ndiag, const int32_t *jd_col, int32_t m, const void *const *h_g,
+                                   const void *const *h_x, const double *h_alpha, void *dval, spmv_dtype dt,
+                                   double beta, const int32_t *tiles, int64_t n_tiles, const int64_t *h_plan,
+                                   unsigned flags, void *ws, size_t ws_bytes, void *stream)
+{
+    SPMV_REQUIRE(n >= 0 && n_cols >= 0 && ndiag >= 0 && n_tiles >= 0, "spmv_grad_vals_jds_sum: negative size");
+    SPMV_REQUIRE(m >= 1 && m <= GRAD_PAIRS, "spmv_grad_vals_jds_sum: m must be in [1, 8]");
+    SPMV_REQUIRE(valid_vec_dtype(dt), "spmv_grad_vals_jds_sum: dtype must be F64 or F32");
+    SPMV_REQUIRE((flags & ~SPMV_SYMPERM) == 0, "spmv_grad_vals_jds_sum: unknown flag");
+    TileBounds xb;
+    int64_t widest = 0;
+    spmv_status st = check_tile_plan(h_plan, n_tiles, xb, &widest,
+                                     "spmv_grad_vals_jds_sum: h_plan bounds or wavefront count invalid");
+    if (st != SPMV_OK) return st;
+    if (n == 0 || n_tiles == 0 || ndiag == 0) return SPMV_OK;
+    SPMV_REQUIRE(jd_ptr && jd_col && dval && tiles && h_g && h_x && h_alpha, "spmv_grad_vals_jds_sum: null pointer");
+    SPMV_REQUIRE((flags & SPMV_SYMPERM) || perm, "spmv_grad_vals_jds_sum: null perm");
+    SPMV_REQUIRE(ws && ws_bytes >= spmv_grad_vals_jds_sum_workspace_size(n_cols, m, dt),
+                 "spmv_grad_vals_jds_sum: workspace too small");
+    SPMV_REQUIRE((reinterpret_cast<uintptr_t>(ws) & 15) == 0, "spmv_grad_vals_jds_sum: ws must be 16-byte aligned");
+    GradPairs p{};
+    p.m = m;
+    for (int j = 0; j < m; ++j) {
+        SPMV_REQUIRE(h_g[j] && h_x[j], "spmv_grad_vals_jds_sum: null vector");
+        p.g[j] = h_g[j];
+        p.x[j] = h_x[j];
+        p.alpha[j] = h_alpha[j];
+    }
+    JdsArgs a{};
+    a.n = n;
+    a.perm = perm;
+    a.jd_ptr = jd_ptr;
+    a.ndiag = ndiag;
+    a.C = 64;
+    a.col = jd_col;
+    a.dval = dval;
+    a.beta = beta;
+    a.symperm = (flags & SPMV_SYMPERM) ? 1 : 0;
+    hipStream_t s = as_stream(stream);
+    const unsigned stage_grid = (unsigned)ceil_div(n_cols, 256), grid = (unsigned)(widest * 8);
+    const unsigned threads = (unsigned)(h_plan[9] * WAVE);
+#define GRAD_SUM(M, T)                                                                                              \
+    do {                                                                                                            \
+        grad_stage_kernel<M, T><<<stage_grid, 256, 0, s>>>(p, n_cols, (GradRow<M, T> *)ws);                          \
+        SPMV_CHECK_LAUNCH("spmv_grad_vals_jds_sum: staging");                                                       \
+        jds_grad_rows_kernel<4, M, T><<<grid, threads, 0, s>>>(a, tiles, xb, p, (const GradRow<M, T> *)ws);          \
+    } while (0)
+    const int M = grad_row_elems(m);
+    if (dt == SPMV_F64) {
+        if (M == 2) GRAD_SUM(2, double);
+        else if (M == 4) GRAD_SUM(4, double);
+        else GRAD_SUM(8, double);
+    } else {
+        if (M == 2) GRAD_SUM(2, float);
+        else if (M == 4) GRAD_SUM(4, float);
+        else GRAD_SUM(8, float);
+    }
+#undef GRAD_SUM
+    SPMV_CHECK_LAUNCH("spmv_grad_vals_jds_sum");
     return SPMV_OK;
 }
 

@@ -628,6 +628,29 @@ def spmv_grad_vals_jds(J: JDS, g: torch.Tensor, x: torch.Tensor, out: Optional[t
     return out
 
 
+def spmv_grad_vals_jds_sum(J: JDS, pairs, out: Optional[torch.Tensor] = None, beta: float = 0.0) -> torch.Tensor:
+    """dval[e] = sum alpha*g[row_e]*x[col_e] (+ beta*dval[e]) over up to
+    GRAD_MAX_PAIRS pairs (alpha, g, x), added in order: the calls of
+    spmv_grad_vals_jds one after the other, in one pass over the entries."""
+    g0 = pairs[0][1]
+    for _, g, x in pairs:
+        _check_dev(g, x)
+        if g.dtype != g0.dtype or x.dtype != g0.dtype or g.numel() < J.n or x.numel() < J.n_cols:
+            raise ValueError(f"g and x must be {g0.dtype} vectors of {J.n} and {J.n_cols} elements")
+    if out is None:
+        if beta != 0.0:
+            raise ValueError("beta != 0 needs out")
+        out = torch.empty(J.nnz, dtype=g0.dtype, device=g0.device)
+    m, dt = len(pairs), dtype_code(g0.dtype)
+    tiles, nt, h_plan = spmv_jds_tiles(J)
+    ws = _ws(_lib.load().spmv_grad_vals_jds_sum_workspace_size(J.n_cols, m, dt), g0.device)
+    call("spmv_grad_vals_jds_sum", J.n, J.n_cols, _p(J.perm), _p(J.jd_ptr), J.ndiag, _p(J.jd_col), m,
+         _ptr_array([g for _, g, _ in pairs]), _ptr_array([x for _, _, x in pairs]),
+         (C.c_double * m)(*[float(a) for a, _, _ in pairs]), _p(out), dt, float(beta), _p(tiles), nt, _h_i64(h_plan),
+         J.flags, _p(ws), ws.numel(), _stream())
+    return out
+
+
 def spmv_stream_triad(a, b, c, s: float):
     call("spmv_stream_triad", a.numel(), _p(b), _p(c), _p(a), float(s), _stream())
 
