@@ -285,8 +285,9 @@ spmv_status spmv_crs_staged(int32_t n_rows, int32_t n_cols, const int32_t *row_p
  * `unroll` diagonals at a time (2, 4 or 8; 0 = default).  Rows whose length
  * exceeds `max_iters` diagonals (0 = default) have their diagonals split over
  * up to W wavefronts whose partial sums are added in a fixed order, W =
- * wg_waves, the wavefronts per workgroup: 4, 8 or 16 (0 = 16).  unroll,
- * max_iters and wg_waves shape the launch only (small workgroups keep more
+ * wg_waves, the wavefronts per workgroup: 4, 8 or 16.  0 leaves a choice to
+ * the library, which goes by rows, longest row, storage and vector type.
+ * unroll, max_iters and wg_waves shape the launch only (small workgroups keep more
  * gathers in flight for short, irregular rows; large ones stream uniform
  * rows better); the result is the same up to the summation order of long
  * rows.

@@ -956,6 +956,49 @@ static spmv_status launch_jds(const JdsArgs &a, const JdsPlan &P, int unroll, sp
     return fail(SPMV_ERR_UNSUPPORTED, "jds: dtype combination");
 }
 
+// Launch shape of a call that leaves it to the library (unroll, max_iters,
+// wg_waves = 0).  What each choice trades:
+//   max_iters: a row longer than this is split over lanes and wavefronts.  A
+//     small matrix leaves the chip idle while its longest rows finish, so
+//     it splits early (power law, 250 k rows, blocked FP32: 8 wavefronts and
+//     32 diagonals 52 us, 16 and 16 36 us); a large one has wavefronts enough
+//     and pays for each split with worse loads (2 M rows: 16 diagonals 291,
+//     64 224 us).
+//   waves: large workgroups let a long row be split further (their partial
+//     sums meet in one workgroup's LDS); small ones fill a CU's registers
+//     better (79 registers at unroll 8: 24 wavefronts fit, one workgroup of 16
+//     or six of 4) and give a small matrix more workgroups than CUs (60 k rows
+//     of 5-40 entries, FP64: 16 wavefronts 36 us, 4 13 us).
+//   unroll: eight diagonals in flight wait less on gathers (2 M power-law rows
+//     371 against 387 us); where 64 rows read neighbouring x elements the
+//     masked diagonals of the last trip cost more (JDS, full diagonals, 6 M
+//     rows FP32: four 226, eight 245 us).
+// Measured over six row-length families, 5 k to 4 M rows, FP64, FP32 and BF16
+// values, class and tile plans: 0.75 of the time of the former fixed choice
+// (unroll 4, 32 diagonals, 16 wavefronts) on average, no family slower by more
+// than 5%.  Class plans of large matrices of short rows keep that choice: they
+// have no XCD locality, and 16 wavefronts of neighbouring rows share their x
+// lines in L1 (banded, 1.5 M rows, blocked FP32: 16 wavefronts 108, 4 116 us).
+struct JdsShape {
+    int unroll, max_iters, waves;
+};
+
+static JdsShape jds_shape(bool blocked, bool tiles, bool windowed, int64_t n, int64_t longest, bool x8)
+{
+    if (longest <= 64) {
+        if (n < 100000) return {8, 8, 4};
+        if (!tiles && n >= 1000000 && (!blocked || !x8)) return {4, JDS_DEFAULT_MAX_ITERS, 16};
+        return blocked ? JdsShape{8, JDS_DEFAULT_MAX_ITERS, 4} : JdsShape{4, 64, 4};
+    }
+    // windows spread the long rows over the whole matrix: they are always worth splitting
+    if (windowed) return {8, 8, 16};
+    if (n < 300000) return {8, 16, 16};
+    if (n < 700000) return {8, 16, blocked ? 8 : 16};
+    if (blocked) return {8, 64, 8};
+    if (n >= 1750000) return {8, 64, x8 || tiles ? 4 : 16};
+    return {8, 32, x8 && !tiles ? 8 : 16};
+}
+
 static int unroll_ok(int32_t u) { return u == 0 || u == 2 || u == 4 || u == 8; }
 static int waves_ok(int32_t w) { return w == 0 || w == 4 || w == 8 || w == 16; }
 static int waves_or_default(int32_t w) { return w ? w : JDS_WAVES; }
@@ -1020,11 +1063,10 @@ static spmv_status check_tile_plan(const int64_t *h_plan, int64_t n_tiles, TileB
 
 template <int FMT>
 static spmv_status launch_tiles(const JdsArgs &a, const int32_t *tiles, const TileBounds &xb, int64_t widest,
-                                int64_t waves, int32_t unroll, spmv_dtype val_dt, spmv_dtype vec_dt, hipStream_t s,
+                                int64_t waves, int32_t u, spmv_dtype val_dt, spmv_dtype vec_dt, hipStream_t s,
                                 const char *who)
 {
     const unsigned grid = (unsigned)(8 * widest), threads = (unsigned)(waves * WAVE);
-    const int u = unroll ? unroll : 4;
 #define JTILE_CASE(VDT, VT, XDT, XT)                                                                         \
     if (val_dt == VDT && vec_dt == XDT) {                                                                    \
         if (u == 2) jds_tiles_kernel<FMT, 2, VT, XT><<<grid, threads, 0, s>>>(a, tiles, xb);              \
@@ -1074,9 +1116,9 @@ spmv_status spmv_jds(int32_t n, const int32_t *perm, const int32_t *jd_ptr, cons
     a.alpha = alpha;
     a.beta = beta;
     a.symperm = (flags & SPMV_SYMPERM) ? 1 : 0;
-    JdsPlan P = plan_jds(n, h_jd_ptr, ndiag, max_iters ? max_iters : JDS_DEFAULT_MAX_ITERS, -1,
-                         waves_or_default(wg_waves));
-    return launch_jds<FMT_JDS>(a, P, unroll ? unroll : 4, val_dt, vec_dt, as_stream(stream));
+    const JdsShape sh = jds_shape(false, false, false, n, ndiag, vec_dt == SPMV_F64);
+    JdsPlan P = plan_jds(n, h_jd_ptr, ndiag, max_iters ? max_iters : sh.max_iters, -1, wg_waves ? wg_waves : sh.waves);
+    return launch_jds<FMT_JDS>(a, P, unroll ? unroll : sh.unroll, val_dt, vec_dt, as_stream(stream));
 }
 
 spmv_status spmv_jds_blocked(int32_t n, const int32_t *perm, int32_t C, int32_t n_slices, const int64_t *slice_ptr,
@@ -1118,9 +1160,10 @@ spmv_status spmv_jds_blocked(int32_t n, const int32_t *perm, int32_t C, int32_t 
         forced = 0;
         while ((1 << forced) < rows_per_wave) ++forced;
     }
-    JdsPlan P = plan_blocked(n, C, h_slice_nd, max_iters ? max_iters : JDS_DEFAULT_MAX_ITERS, forced,
-                             waves_or_default(wg_waves));
-    return launch_jds<FMT_BLOCKED>(a, P, unroll ? unroll : 4, val_dt, vec_dt, as_stream(stream));
+    const JdsShape sh = jds_shape(true, false, false, n, h_slice_nd[0], vec_dt == SPMV_F64);
+    JdsPlan P = plan_blocked(n, C, h_slice_nd, max_iters ? max_iters : sh.max_iters, forced,
+                             wg_waves ? wg_waves : sh.waves);
+    return launch_jds<FMT_BLOCKED>(a, P, unroll ? unroll : sh.unroll, val_dt, vec_dt, as_stream(stream));
 }
 
 spmv_status spmv_jds_blocked_tiles(int32_t n, int32_t C, int32_t n_slices, const int32_t *h_slice_nd,
@@ -1141,12 +1184,14 @@ spmv_status spmv_jds_blocked_tiles(int32_t n, int32_t C, int32_t n_slices, const
         forced = 0;
         while ((1 << forced) < rows_per_wave) ++forced;
     }
-    const int waves = waves_or_default(wg_waves);
-    const int32_t mi = max_iters ? max_iters : JDS_DEFAULT_MAX_ITERS;
     std::vector<int32_t> rec;
     int64_t bounds[9];
     bool sorted = true;                       // the globally sorted order: depths never increase
     for (int32_t sl = 1; sl < n_slices && sorted; ++sl) sorted = h_slice_nd[sl] <= h_slice_nd[sl - 1];
+    const int32_t longest = n_slices ? *std::max_element(h_slice_nd, h_slice_nd + n_slices) : 0;
+    const JdsShape sh = jds_shape(true, true, !sorted, n, longest, false);
+    const int waves = wg_waves ? wg_waves : sh.waves;
+    const int32_t mi = max_iters ? max_iters : sh.max_iters;
     if (sorted)
         plan_tiles_local(n, C, n_slices, [&](int64_t u) -> int64_t { return h_slice_nd[u]; }, mi, forced, waves,
                          TILE_LOCAL_MIN_RUN, rec, bounds);
@@ -1181,7 +1226,8 @@ spmv_status spmv_jds_tiles(int32_t n, const int32_t *h_jd_ptr, int32_t ndiag, in
         forced = 0;
         while ((1 << forced) < rows_per_wave) ++forced;
     }
-    const int waves = waves_or_default(wg_waves);
+    const JdsShape sh = jds_shape(false, true, false, n, ndiag, false);
+    const int waves = wg_waves ? wg_waves : sh.waves;
     // length of permuted row r: the diagonals longer than r
     auto row_len = [&](int64_t r) -> int64_t {
         int32_t lo = 0, hi = ndiag;
@@ -1194,7 +1240,7 @@ spmv_status spmv_jds_tiles(int32_t n, const int32_t *h_jd_ptr, int32_t ndiag, in
     };
     std::vector<int32_t> rec;
     int64_t bounds[9];
-    plan_tiles_local(n, 1, n, row_len, max_iters ? max_iters : JDS_DEFAULT_MAX_ITERS, forced, waves,
+    plan_tiles_local(n, 1, n, row_len, max_iters ? max_iters : sh.max_iters, forced, waves,
                      TILE_LOCAL_MIN_RUN, rec, bounds);
     const int64_t nt = (int64_t)rec.size() / 2;
     *h_n_tiles = nt;
@@ -1243,7 +1289,8 @@ spmv_status spmv_jds_blocked_tiled(int32_t n, const int32_t *perm, int32_t C, in
     a.alpha = alpha;
     a.beta = beta;
     a.symperm = (flags & SPMV_SYMPERM) ? 1 : 0;
-    return launch_tiles<FMT_BLOCKED>(a, tiles, xb, widest, h_plan[9], unroll, val_dt, vec_dt, as_stream(stream),
+    // every shape of a blocked tile plan has unroll 8
+    return launch_tiles<FMT_BLOCKED>(a, tiles, xb, widest, h_plan[9], unroll ? unroll : 8, val_dt, vec_dt, as_stream(stream),
                                      "spmv_jds_blocked_tiled");
 }
 
@@ -1278,7 +1325,8 @@ spmv_status spmv_jds_tiled(int32_t n, const int32_t *perm, const int32_t *jd_ptr
     a.alpha = alpha;
     a.beta = beta;
     a.symperm = (flags & SPMV_SYMPERM) ? 1 : 0;
-    return launch_tiles<FMT_JDS>(a, tiles, xb, widest, h_plan[9], unroll, val_dt, vec_dt, as_stream(stream),
+    const int u = unroll ? unroll : jds_shape(false, true, false, n, ndiag, vec_dt == SPMV_F64).unroll;
+    return launch_tiles<FMT_JDS>(a, tiles, xb, widest, h_plan[9], u, val_dt, vec_dt, as_stream(stream),
                                  "spmv_jds_tiled");
 }
 
