@@ -223,10 +223,12 @@ spmv_status spmv_crs_plan(int32_t n_rows, const int32_t *row_ptr, int32_t block_
  * instead of its copy to the host and back.  2 * ceil(nnz / block_nnz) +
  * n_rows / 256 + 2 int32 always hold the plan.  If plan_cap < n_blocks+1
  * returns SPMV_ERR_CAPACITY with *h_n_blocks set (plan may hold a part of
- * the boundaries then).  Synchronises. */
+ * the boundaries then).  h_longest (may be NULL) gets the longest row.
+ * Synchronises. */
 size_t spmv_crs_plan_workspace_size(int32_t n_rows);
 spmv_status spmv_crs_plan_ws(int32_t n_rows, const int32_t *row_ptr, int32_t block_nnz, int32_t *plan,
-                             int32_t plan_cap, int32_t *h_n_blocks, void *ws, size_t ws_bytes, void *stream);
+                             int32_t plan_cap, int32_t *h_n_blocks, int32_t *h_longest, void *ws, size_t ws_bytes,
+                             void *stream);
 
 /* CRS <-> reduced-precision value conversion: out[i] = in[i] rounded to
  * out_dt with round-to-nearest-even in one step (F64 -> BF16 does not pass

@@ -52,7 +52,7 @@ SIGNATURES = {
     "spmv_jds_blocked_from_jds": (_int, [_i32, _p, _i32, _p, _p, _int, _i32, _u32, _p, _p, _p, _p, _i64, _i64p,
                                          _i32p, _p, _sz, _p]),
     "spmv_crs_plan_workspace_size": (_sz, [_i32]),
-    "spmv_crs_plan_ws": (_int, [_i32, _p, _i32, _p, _i32, _i32p, _p, _sz, _p]),
+    "spmv_crs_plan_ws": (_int, [_i32, _p, _i32, _p, _i32, _i32p, _i32p, _p, _sz, _p]),
     "spmv_crs_plan": (_int, [_i32, _p, _i32, _p, _i32, _i32p, _p]),
     "spmv_jds_blocked_windowed_workspace_size": (_sz, [_i32]),
     "spmv_jds_blocked_windowed_from_csr": (_int, [_i32, _i64, _p, _p, _p, _int, _i32, _i32, _p, _p, _p, _p, _p,

@@ -28,6 +28,16 @@ from . import spmv as S
 from ._lib import GRAD_MAX_PAIRS
 
 
+# The product with A^T gathers in row order (the staged kernel) when no row is
+# long: neighbouring rows' entries at one position then share x lines.  A^T of
+# a banded matrix with a few far entries (n = 4 M, 20 per row) takes 438 us in
+# entry order and 379 us staged with blocks of 2,048 entries in FP32, 542 and
+# 469 us in FP64; the A^T of power-law rows 112.7 and 110.0 us, of uniform rows
+# 247.7 and 253.8 us (n = 1.5 M).  Rows of thousands of entries, which one group
+# of lanes walks, cost more than that saves (2 M power-law rows: 252 and 415 us).
+STAGED_LONGEST, STAGED_BLOCK = 64, 2048
+
+
 class SpMVOperator:
     def __init__(self, A: S.CSR, unroll: int = 0, max_iters: int = 0, transpose: str = "crs", wg_waves: int = 0):
         if A.n_rows != A.n_cols:
@@ -52,6 +62,9 @@ class SpMVOperator:
             # A^T CRS slot -> A CRS position -> A JDS slot
             self.tmapT = S.spmv_gather_values(tmap, jds_of_crs)
             self.AT = S.spmv_crs_plan(S.CSR(A.n_cols, A.n_rows, rowT, colT, None))
+            if 0 < self.AT.longest <= STAGED_LONGEST:
+                S.spmv_crs_plan(self.AT, STAGED_BLOCK)
+                self.AT.staged = True
             self.JT = None
         else:
             AT = S.CSR(A.n_cols, A.n_rows, rowT, colT, tmap)

@@ -32,14 +32,15 @@ struct PlanEntry {
 };
 
 // step[r] = rows of the block that starts at row r; table[tile][e] as above;
-// bad[0] = 1 if row_ptr decreases.
+// result[1] = 1 if row_ptr decreases, result[2]: longest row.
 __global__ __launch_bounds__(PT_THREADS) void plan_tiles_kernel(const int32_t *__restrict__ rp, int32_t n, int32_t T,
                                                                 uint16_t *__restrict__ step,
                                                                 PlanEntry *__restrict__ table,
-                                                                int32_t *__restrict__ bad)
+                                                                int32_t *__restrict__ result)
 {
     __shared__ int32_t p[PT_ROWS + PT_SPAN + 1];
     __shared__ uint32_t jump[PT_ROWS];                     // rows past the tile's start | blocks << 16
+    __shared__ int32_t wmax[PT_THREADS / WAVE];
     __shared__ uint64_t longer[PT_WORDS];                  // bit r: row r has more than CRS_SHORT_ROW entries
     const int t = (int)threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * PT_ROWS;
@@ -48,14 +49,22 @@ __global__ __launch_bounds__(PT_THREADS) void plan_tiles_kernel(const int32_t *_
     for (int32_t i = t; i <= left; i += PT_THREADS) p[i] = rp[base + i];
     __syncthreads();
     bool dec = false;
+    int32_t longest = 0;
     for (int32_t i = t; i < PT_ROWS + PT_SPAN; i += PT_THREADS) {          // whole wavefronts
         const int32_t len = i < left ? p[i + 1] - p[i] : 0;
         dec |= len < 0;
+        longest = i < rows && len > longest ? len : longest;
         const uint64_t m = __ballot(len > CRS_SHORT_ROW);
         if (lane_id() == 0) longer[i / WAVE] = m;
     }
-    if (__ballot(dec) && lane_id() == 0) atomicOr(bad, 1);
+    if (__ballot(dec) && lane_id() == 0) atomicOr(result + 1, 1);
+    for (int off = WAVE / 2; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off, WAVE));
+    if (lane_id() == 0) wmax[t / WAVE] = longest;
     __syncthreads();
+    if (t == 0) {
+        for (int q = 1; q < PT_THREADS / WAVE; ++q) longest = max(longest, wmax[q]);
+        atomicMax(result + 2, longest);
+    }
     for (int32_t r = t; r < rows; r += PT_THREADS) {
         // most rows: 256, or up to the first longer row, at most 2048
         const int32_t most = left < r + PT_SPAN ? left : r + PT_SPAN;
@@ -170,12 +179,13 @@ size_t spmv_crs_plan_workspace_size(int32_t n_rows)
 {
     const size_t n = (size_t)(n_rows > 0 ? n_rows : 1);
     const size_t tiles = (size_t)plan_tile_count(n_rows), groups = (size_t)ceil_div((int64_t)tiles, PT_GROUP);
-    return align_up(2 * sizeof(int32_t), 256) + align_up(sizeof(uint16_t) * n, 256) +
+    return align_up(3 * sizeof(int32_t), 256) + align_up(sizeof(uint16_t) * n, 256) +
            align_up(sizeof(PlanEntry) * PT_SPAN * tiles, 256) + align_up(sizeof(PlanEntry) * PT_SPAN * groups, 256) + 256;
 }
 
 spmv_status spmv_crs_plan_ws(int32_t n_rows, const int32_t *row_ptr, int32_t block_nnz, int32_t *plan,
-                             int32_t plan_cap, int32_t *h_n_blocks, void *ws, size_t ws_bytes, void *stream)
+                             int32_t plan_cap, int32_t *h_n_blocks, int32_t *h_longest, void *ws, size_t ws_bytes,
+                             void *stream)
 {
     SPMV_REQUIRE(n_rows >= 0, "spmv_crs_plan_ws: n_rows < 0");
     SPMV_REQUIRE(h_n_blocks, "spmv_crs_plan_ws: null h_n_blocks");
@@ -188,6 +198,7 @@ spmv_status spmv_crs_plan_ws(int32_t n_rows, const int32_t *row_ptr, int32_t blo
     hipStream_t s = as_stream(stream);
     if (n_rows == 0) {
         *h_n_blocks = 0;
+        if (h_longest) *h_longest = 0;
         if (plan_cap < 1) return fail(SPMV_ERR_CAPACITY, "spmv_crs_plan_ws: plan capacity < n_blocks+1");
         SPMV_HIP(hipMemsetAsync(plan, 0, sizeof(int32_t), s));
         SPMV_HIP(hipStreamSynchronize(s));
@@ -195,13 +206,13 @@ spmv_status spmv_crs_plan_ws(int32_t n_rows, const int32_t *row_ptr, int32_t blo
     }
     const int64_t tiles = plan_tile_count(n_rows), groups = ceil_div(tiles, PT_GROUP);
     WsCarver wc(ws, ws_bytes);
-    int32_t *result = wc.take<int32_t>(2);                   // number of blocks, row_ptr decreases
+    int32_t *result = wc.take<int32_t>(3);                   // number of blocks, row_ptr decreases, longest row
     uint16_t *step = wc.take<uint16_t>((size_t)n_rows);
     PlanEntry *table = wc.take<PlanEntry>((size_t)tiles * PT_SPAN);
     PlanEntry *group_table = wc.take<PlanEntry>((size_t)groups * PT_SPAN);
     if (!wc.ok()) return fail(SPMV_ERR_INVALID_ARG, "spmv_crs_plan_ws: workspace too small");
-    SPMV_HIP(hipMemsetAsync(result, 0, 2 * sizeof(int32_t), s));
-    plan_tiles_kernel<<<(unsigned)tiles, PT_THREADS, 0, s>>>(row_ptr, n_rows, block_nnz, step, table, result + 1);
+    SPMV_HIP(hipMemsetAsync(result, 0, 3 * sizeof(int32_t), s));
+    plan_tiles_kernel<<<(unsigned)tiles, PT_THREADS, 0, s>>>(row_ptr, n_rows, block_nnz, step, table, result);
     SPMV_CHECK_LAUNCH("crs plan tiles");
     if (groups > 1) {
         plan_groups_kernel<<<dim3(PT_SPAN / 256, (unsigned)groups), 256, 0, s>>>(table, tiles, group_table);
@@ -209,11 +220,12 @@ spmv_status spmv_crs_plan_ws(int32_t n_rows, const int32_t *row_ptr, int32_t blo
     }
     plan_write_kernel<<<(unsigned)tiles, 256, 0, s>>>(step, n_rows, table, group_table, tiles, plan, plan_cap, result);
     SPMV_CHECK_LAUNCH("crs plan");
-    int32_t h[2] = {0, 0};
+    int32_t h[3] = {0, 0, 0};
     SPMV_HIP(hipMemcpyAsync(h, result, sizeof(h), hipMemcpyDeviceToHost, s));
     SPMV_HIP(hipStreamSynchronize(s));
     if (h[1]) return fail(SPMV_ERR_BAD_FORMAT, "spmv_crs_plan_ws: row_ptr decreases");
     *h_n_blocks = h[0];
+    if (h_longest) *h_longest = h[2];
     if (plan_cap < h[0] + 1) return fail(SPMV_ERR_CAPACITY, "spmv_crs_plan_ws: plan capacity < n_blocks+1");
     return SPMV_OK;
 }

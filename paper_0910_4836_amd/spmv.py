@@ -89,6 +89,7 @@ class CSR:
     n_blocks: int = 0
     block_nnz: int = 0
     staged: bool = False        # spmv_crs runs the staged kernel (spmv_crs_staged) over the plan
+    longest: int = -1           # entries of the longest row, once a plan has been built
 
     @property
     def nnz(self) -> int:
@@ -100,7 +101,7 @@ class CSR:
 
     def with_values(self, val: torch.Tensor) -> "CSR":
         return CSR(self.n_rows, self.n_cols, self.row_ptr, self.col_idx, val, self.plan, self.n_blocks,
-                   self.block_nnz, self.staged)
+                   self.block_nnz, self.staged, self.longest)
 
 
 @dataclass
@@ -195,11 +196,12 @@ def spmv_csr_validate(A: CSR) -> bool:
 def spmv_crs_plan(A: CSR, block_nnz: int = 0) -> CSR:
     """Builds (and stores on A) the row-block plan used by spmv_crs / spmm_crs."""
     lib = _lib.load()
-    nb = C.c_int32(0)
+    nb, longest = C.c_int32(0), C.c_int32(0)
     ws = _ws(lib.spmv_crs_plan_workspace_size(A.n_rows), A.device)
     # a block and the row after it hold more than block_nnz entries, or the block has at least 256 rows
     cap = 2 * -(-A.nnz // max(block_nnz or 1024, 1)) + A.n_rows // 256 + 2
-    args = lambda p: (A.n_rows, _p(A.row_ptr), block_nnz, _p(p), p.numel(), C.byref(nb), _p(ws), ws.numel(), _stream())
+    args = lambda p: (A.n_rows, _p(A.row_ptr), block_nnz, _p(p), p.numel(), C.byref(nb),
+                      C.byref(longest), _p(ws), ws.numel(), _stream())
     plan = torch.empty(cap, dtype=_I32, device=A.device)
     st = lib.spmv_crs_plan_ws(*args(plan))
     if st != 0:
@@ -207,7 +209,7 @@ def spmv_crs_plan(A: CSR, block_nnz: int = 0) -> CSR:
             plan = torch.empty(nb.value + 1, dtype=_I32, device=A.device)
         call("spmv_crs_plan_ws", *args(plan))
     plan = plan[:nb.value + 1]
-    A.plan, A.n_blocks, A.block_nnz = plan, nb.value, block_nnz
+    A.plan, A.n_blocks, A.block_nnz, A.longest = plan, nb.value, block_nnz, longest.value
     return A
 
 

@@ -168,3 +168,10 @@ def test_jds_and_blocked_at_tile_edges(shape, dtype):
         assert np.array_equal(to_np(K.slice_ptr), RK.slice_ptr)
         assert np.array_equal(to_np(K.bl_col), RK.bl_col)
         assert np.array_equal(to_np(K.bl_val.double()), RK.bl_val)
+
+
+@pytest.mark.parametrize("n", [1, 4096, 4097, 20_000])
+def test_plan_reports_the_longest_row(n):
+    lengths = np.random.default_rng(n).integers(0, 30, n)
+    lengths[n // 2] = 77
+    assert sp.spmv_crs_plan(csr_of_lengths(lengths)).longest == 77
