@@ -4,9 +4,9 @@
 // from k far-apart columns: k L2 lines per entry.  With a workspace the
 // library first copies X into an interleaved (row-major) block Xr, one
 // transposing pass at streaming speed, and then every entry gathers its k
-// values as one contiguous run of k*8 bytes.  Each row is handled by a group
-// of LPR lanes (K2 = k rounded up to a power of two, at most 64; LPR = K2 up
-// to 8, then 8 or 16), lane j owning columns j, j + LPR, ...: val/col are read
+// values as one contiguous run of k*8 bytes (rows of Xr are padded where that
+// keeps them in one line, mm_padded_ld).  Each row is handled by a group
+// of LPR lanes (K2 = k rounded up: k2_for; LPR = K2 up to 8, then 8 or 16), lane j owning columns j, j + LPR, ...: val/col are read
 // once per entry for all k columns and each gather load of a group is
 // contiguous.  Long rows get several groups whose partial sums meet in LDS and
 // are added in a fixed order.  Y is written column-major directly.
@@ -18,7 +18,6 @@
 #include "common.hpp"
 
 namespace spmv {
-
 // Workgroup sizes, measured on the power-law matrix: the CRS kernel's rows
 // are handled in rounds that each wait on their gathers, and 128-lane groups
 // for k <= 8 keep more rounds in flight (10-14% faster than 256); the JDS
@@ -56,9 +55,9 @@ constexpr int MM_YTILE_ELEMS = 1024;
 template <int K2>
 constexpr size_t mm_ytile_bytes() { return K2 >= 16 ? sizeof(double) * MM_YTILE_ELEMS + 16 : 0; }
 
-// Xr[c*k + j] = X[c + j*ldx] (2 <= k <= 64): a block of STAGE_ELEMS / k rows
+// Xr[c*ld + j] = X[c + j*ldx] (2 <= k <= 64): a block of STAGE_ELEMS / k rows
 // through LDS.  Reads walk each column's run of rows (coalesced), writes walk
-// the block's contiguous stretch of Xr (coalesced).  Each lane issues all
+// the block's rows of Xr (coalesced).  Each lane issues all
 // of its STAGE_PER_LANE reads before its LDS stores, and all of its LDS reads
 // before its global stores, so a lane keeps 8 loads in flight.  (k = 1
 // needs no staging: X itself is the row-major block.)
@@ -68,7 +67,7 @@ constexpr int STAGE_PER_LANE = STAGE_ELEMS / STAGE_THREADS;
 
 template <typename T>
 __global__ __launch_bounds__(STAGE_THREADS) void stage_rowmajor_kernel(int64_t n, int32_t k, const T *__restrict__ X,
-                                                                       int64_t ldx, T *__restrict__ Xr)
+                                                                       int64_t ldx, T *__restrict__ Xr, int32_t ld)
 {
     __shared__ T tile[STAGE_ELEMS + STAGE_ELEMS / 2];   // rows * (k + 1) for k >= 2
     const int rows = STAGE_ELEMS / k;                   // rows of this block
@@ -91,6 +90,7 @@ __global__ __launch_bounds__(STAGE_THREADS) void stage_rowmajor_kernel(int64_t n
         if (r < nr && j < k) tile[r * stride + j] = v[e];
     }
     __syncthreads();
+    T *out = Xr + c0 * ld;
 #pragma unroll
     for (int e = 0; e < STAGE_PER_LANE; ++e) {
         const int f = min(t + e * STAGE_THREADS, tot - 1);
@@ -99,21 +99,37 @@ __global__ __launch_bounds__(STAGE_THREADS) void stage_rowmajor_kernel(int64_t n
 #pragma unroll
     for (int e = 0; e < STAGE_PER_LANE; ++e) {
         const int f = t + e * STAGE_THREADS;
-        if (f < tot) Xr[c0 * k + f] = v[e];
+        if (f < tot) out[f + (ld > k ? f / k * (ld - k) : 0)] = v[e];
     }
+}
+
+// Lane j's columns j, j + LPR, ..., those past the last clamped to it: a lane
+// that has no such column gathers its neighbour's element again (the same
+// line) and never writes the sum.  A guard instead of the clamp puts every
+// gather behind a branch of its own, which the scheduler does not move loads
+// across (CRS, 2 M power-law rows, k = 8, FP32: 956 us with the guard, 578
+// with the clamp; windowed, k = 13: 833 and 735).  The JDS kernel keeps its
+// guard, which the entry's own mask needs anyway (no difference measured).
+template <int LPR, int CPL>
+__device__ __forceinline__ void mm_columns(int32_t (&cj)[CPL], int32_t k, int j)
+{
+#pragma unroll
+    for (int t = 0; t < CPL; ++t) cj[t] = min(t * LPR + j, k - 1);
 }
 
 // One group of LPR lanes per (row, part): lane j accumulates columns j,
 // j + LPR, ..., j + (CPL-1)*LPR over entries e_begin, e_begin + e_step, ...
 template <int LPR, int CPL, bool WIDE, typename VT, typename XT>
 __device__ __forceinline__ void mm_group_sum(const int32_t *__restrict__ col, const VT *__restrict__ val,
-                                             const XT *__restrict__ Xr, int32_t k, int j, int64_t e_begin,
+                                             const XT *__restrict__ Xr, int32_t ld, int32_t k, int j, int64_t e_begin,
                                              int64_t e_end, int64_t e_step, double (&out)[CPL])
 {
     typedef typename Acc<WIDE>::T acc_t;
     acc_t s[CPL];
 #pragma unroll
     for (int t = 0; t < CPL; ++t) s[t] = 0;
+    int32_t cj[CPL];
+    mm_columns<LPR, CPL>(cj, k, j);
     // entries per trip: eight gathers in flight per lane (U * CPL = 8);
     // measured at k = 8 (U = 8: 4-11% faster than 4) and k = 32 FP32 (U = 2)
     constexpr int U = CPL >= 8 ? 1 : 8 / CPL;
@@ -131,7 +147,7 @@ __device__ __forceinline__ void mm_group_sum(const int32_t *__restrict__ col, co
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int t = 0; t < CPL; ++t)
-                xv[u][t] = t * LPR + j < k ? Xr[(int64_t)c[u] * k + t * LPR + j] : XT(0);
+                xv[u][t] = Xr[(int64_t)c[u] * ld + cj[t]];
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -142,8 +158,7 @@ __device__ __forceinline__ void mm_group_sum(const int32_t *__restrict__ col, co
         const VT v = val[e];
 #pragma unroll
         for (int t = 0; t < CPL; ++t) {
-            const XT xv = t * LPR + j < k ? Xr[(int64_t)c * k + t * LPR + j] : XT(0);
-            s[t] = Acc<WIDE>::mac(s[t], v, xv);
+            s[t] = Acc<WIDE>::mac(s[t], v, Xr[(int64_t)c * ld + cj[t]]);
         }
     }
 #pragma unroll
@@ -162,12 +177,14 @@ __device__ __forceinline__ void mm_group_sum(const int32_t *__restrict__ col, co
 template <int LPR, int CPL, int NG, int K2, bool WIDE, typename VT, typename XT>
 __device__ __forceinline__ void mm_crs_balanced(const int32_t *rp, int32_t r0, int32_t r1,
                                                 const int32_t *col_s, const VT *val_s,
-                                                const XT *__restrict__ Xr, int32_t k, XT *__restrict__ Y,
+                                                const XT *__restrict__ Xr, int32_t ld, int32_t k, XT *__restrict__ Y,
                                                 int64_t ldy, double alpha, double beta, int g, int j,
                                                 double (*lead)[K2], double (*tail)[K2], int32_t *lead_row,
                                                 int32_t *tail_row, double *ytile)
 {
     typedef typename Acc<WIDE>::T acc_t;
+    int32_t cj[CPL];
+    mm_columns<LPR, CPL>(cj, k, j);
     constexpr int U = CPL >= 8 ? 1 : 8 / CPL;
     const int32_t E = rp[r1 - r0];
     const int32_t cs = (int32_t)((int64_t)g * E / NG), ce = (int32_t)((int64_t)(g + 1) * E / NG);
@@ -226,7 +243,7 @@ __device__ __forceinline__ void mm_crs_balanced(const int32_t *rp, int32_t r0, i
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int t = 0; t < CPL; ++t)
-                    xv[u][t] = t * LPR + j < k ? Xr[(int64_t)c[u] * k + t * LPR + j] : XT(0);
+                    xv[u][t] = Xr[(int64_t)c[u] * ld + cj[t]];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (e + u >= ce) break;
@@ -306,7 +323,7 @@ template <int K2, int NT, typename VT, typename XT>
 __global__ __launch_bounds__(NT) void spmm_crs_il_kernel(const int32_t *__restrict__ row_ptr,
                                                                  const int32_t *__restrict__ col,
                                                                  const VT *__restrict__ val,
-                                                                 const XT *__restrict__ Xr, int32_t k,
+                                                                 const XT *__restrict__ Xr, int32_t ld, int32_t k,
                                                                  XT *__restrict__ Y, int64_t ldy,
                                                                  const int32_t *__restrict__ plan, int32_t block_nnz,
                                                                  double alpha, double beta)
@@ -359,7 +376,7 @@ __global__ __launch_bounds__(NT) void spmm_crs_il_kernel(const int32_t *__restri
                 // after the row offsets, rounded up to 16 bytes
                 const uintptr_t tile_at = ((uintptr_t)(rp_s + mm_rp_lds(block_nnz) + 1) + 15) & ~(uintptr_t)15;
                 double *ytile = K2 >= 16 && nr * K2 <= MM_YTILE_ELEMS ? reinterpret_cast<double *>(tile_at) : nullptr;
-                mm_crs_balanced<LPR, CPL, NG, K2, F64, VT, XT>(rp_s, r0, r1, col_s, val_s, Xr, k, Y, ldy, alpha,
+                mm_crs_balanced<LPR, CPL, NG, K2, F64, VT, XT>(rp_s, r0, r1, col_s, val_s, Xr, ld, k, Y, ldy, alpha,
                                                                beta, g, j, part, tailp, lead_row, tail_row, ytile);
                 return;
             }
@@ -374,12 +391,12 @@ __global__ __launch_bounds__(NT) void spmm_crs_il_kernel(const int32_t *__restri
             const int32_t e0 = rp_lds ? rp_s[row - r0] + be0 : row_ptr[row];
             const int32_t e1 = rp_lds ? rp_s[row + 1 - r0] + be0 : row_ptr[row + 1];
             if (staged) {
-                if (F64) mm_group_sum<LPR, CPL, true, VT, XT>(col_s, val_s, Xr, k, j, e0 - be0 + sub, e1 - be0, GPR, td);
-                else mm_group_sum<LPR, CPL, false, VT, XT>(col_s, val_s, Xr, k, j, e0 - be0 + sub, e1 - be0, GPR, td);
+                if (F64) mm_group_sum<LPR, CPL, true, VT, XT>(col_s, val_s, Xr, ld, k, j, e0 - be0 + sub, e1 - be0, GPR, td);
+                else mm_group_sum<LPR, CPL, false, VT, XT>(col_s, val_s, Xr, ld, k, j, e0 - be0 + sub, e1 - be0, GPR, td);
             } else if (F64 || wide) {
-                mm_group_sum<LPR, CPL, true, VT, XT>(col, val, Xr, k, j, e0 + sub, e1, GPR, td);
+                mm_group_sum<LPR, CPL, true, VT, XT>(col, val, Xr, ld, k, j, e0 + sub, e1, GPR, td);
             } else {
-                mm_group_sum<LPR, CPL, false, VT, XT>(col, val, Xr, k, j, e0 + sub, e1, GPR, td);
+                mm_group_sum<LPR, CPL, false, VT, XT>(col, val, Xr, ld, k, j, e0 + sub, e1, GPR, td);
             }
         }
         if (GPR > 1) {
@@ -411,15 +428,27 @@ __global__ __launch_bounds__(NT) void spmm_crs_il_kernel(const int32_t *__restri
 }
 
 // JDS, interleaved X.  The host splits the permuted rows (longest first) into
-// classes with GPR wavefronts per row set (enough that each handles at most
-// about 32 of a row's diagonals, GPR <= wavefronts per workgroup); a
-// workgroup holds NG/GPR rows of a class.
+// classes with GPR wavefronts per row set and D lane groups per row in each,
+// enough that a group handles at most 32 of a row's diagonals (16 where the
+// matrix is small), GPR <= wavefronts per workgroup; a workgroup holds
+// NG/(GPR*D) rows of a class.
+// D > 1 only below MM_SMALL_ROWS rows: there the chain of the longest rows is
+// the time (power-law rows, k = 8, FP32, D = 1 to D <= 8: 100 k rows 151 to
+// 53 us, 20 k rows 117 to 21 us).  At size other rows hide it, and D groups
+// read D times as many runs of a diagonal, each D times as short (2 M rows,
+// k = 8, FP32: 734 us at D = 1, 861 with D <= 4 and no class split finer than
+// 32 diagonals).  Between MM_TINY_ROWS and MM_SMALL_ROWS half as many groups
+// (250 k rows, k = 8: D <= 4 106 us, D <= 8 124, D = 1 190).
+constexpr int64_t MM_SMALL_ROWS = 300000;
+constexpr int64_t MM_TINY_ROWS = 150000;
 struct MmClass {
     int32_t wg_end, row_start, row_end, gpr;
+    int32_t log_d;      // log2 of the lane groups per row inside a wavefront
     int32_t len0;       // diagonals of the class's first (longest) row
 };
+constexpr int MM_CLASSES = 10;             // groups per row: 1, 2, ..., 8 wavefronts of 64 groups
 struct MmPlan {
-    MmClass c[8];
+    MmClass c[MM_CLASSES];
     int32_t ncls;
 };
 
@@ -428,14 +457,13 @@ struct MmPlan {
 // of row r, U per trip, stopping (for the whole wavefront) where the
 // wavefront's first and longest row r_first ends.  Column t*LPR + j of the
 // row's LPR lanes is one contiguous run of LPR elements per load.
-template <int LPR, int CPL, bool WIDE, typename VT, typename XT>
+template <int LPR, int CPL, int U, bool WIDE, typename VT, typename XT>
 __device__ __forceinline__ void mm_jds_sum(const int32_t *__restrict__ jp, int32_t dlim,
                                            const int32_t *__restrict__ col, const VT *__restrict__ val,
-                                           const XT *__restrict__ Xr, int32_t k, int j, int32_t r, bool ok,
-                                           int32_t r_first, int sub, int GPR, double (&out)[CPL])
+                                           const XT *__restrict__ Xr, int32_t ld, int32_t k, int j, int32_t r,
+                                           bool ok, int32_t r_first, int sub, int GPR, double (&out)[CPL])
 {
     typedef typename Acc<WIDE>::T acc_t;
-    constexpr int U = 2;   // diagonals per trip (2 measured 1-2% faster than 4, 8 slower)
     acc_t s[CPL];
 #pragma unroll
     for (int t = 0; t < CPL; ++t) s[t] = 0;
@@ -462,7 +490,7 @@ __device__ __forceinline__ void mm_jds_sum(const int32_t *__restrict__ jp, int32
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int t = 0; t < CPL; ++t)
-                xv[u][t] = (act[u] && t * LPR + j < k) ? Xr[(int64_t)c[u] * k + t * LPR + j] : XT(0);
+                xv[u][t] = (act[u] && t * LPR + j < k) ? Xr[(int64_t)c[u] * ld + t * LPR + j] : XT(0);
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (act[u]) {
@@ -474,12 +502,12 @@ __device__ __forceinline__ void mm_jds_sum(const int32_t *__restrict__ jp, int32
     for (int t = 0; t < CPL; ++t) out[t] = (double)s[t];
 }
 
-template <int K2, int NT, typename VT, typename XT>
+template <int K2, bool SMALL, int NT, typename VT, typename XT>
 __global__ __launch_bounds__(NT) void spmm_jds_il_kernel(int32_t ndiag, const int32_t *__restrict__ jp,
                                                                  const int32_t *__restrict__ perm, int symperm,
                                                                  const int32_t *__restrict__ col,
                                                                  const VT *__restrict__ val,
-                                                                 const XT *__restrict__ Xr, int32_t k,
+                                                                 const XT *__restrict__ Xr, int32_t ld, int32_t k,
                                                                  XT *__restrict__ Y, int64_t ldy, MmPlan P,
                                                                  double alpha, double beta)
 {
@@ -490,6 +518,9 @@ __global__ __launch_bounds__(NT) void spmm_jds_il_kernel(int32_t ndiag, const in
     constexpr int NG = NT / LPR;
     constexpr int GPW = WAVE / LPR;            // rows per wavefront
     constexpr bool F64 = IsF64<VT>::value;
+    // diagonals per trip: two at size (4: 1-3% slower, 8 more), four where few
+    // wavefronts are in flight (2: 3-30% slower at 20 k rows)
+    constexpr int U = SMALL ? 4 : 2;
     __shared__ double part[NG][K2];
     const int64_t wg = blockIdx.x;
     int ci = 0;
@@ -499,11 +530,11 @@ __global__ __launch_bounds__(NT) void spmm_jds_il_kernel(int32_t ndiag, const in
     // a wavefront always holds GPW consecutive rows, so every val/col load
     // of one diagonal covers GPW consecutive entries; a row set's diagonals
     // are shared by GPR wavefronts (sub = 0..GPR-1, every GPR-th diagonal)
-    const int GPR = K.gpr;
+    const int GPR = K.gpr, log_d = SMALL ? K.log_d : 0, D = 1 << log_d, RPW = GPW >> log_d;
     const int g = (int)threadIdx.x / LPR, j = (int)threadIdx.x % LPR;
-    const int w = (int)threadIdx.x / WAVE, gl = g % GPW;
+    const int w = (int)threadIdx.x / WAVE, gl = g & (RPW - 1), dl = SMALL ? (g & (GPW - 1)) / RPW : 0;
     const int sub = w % GPR, rs = w / GPR;
-    const int64_t rs0 = (int64_t)K.row_start + (wg - wg0) * (NG / GPR) + (int64_t)rs * GPW;
+    const int64_t rs0 = (int64_t)K.row_start + (wg - wg0) * (NG / (GPR * D)) + (int64_t)rs * RPW;
     const int64_t row64 = rs0 + gl;
     const bool ok = row64 < K.row_end;
     const int32_t r = (int32_t)(ok ? row64 : 0);
@@ -524,17 +555,22 @@ __global__ __launch_bounds__(NT) void spmm_jds_il_kernel(int32_t ndiag, const in
     }
     double td[CPL];
     if (jp_lds) {
-        if (F64 || wide) mm_jds_sum<LPR, CPL, true, VT, XT>(jp_s, dlim, col, val, Xr, k, j, r, ok, r_first, sub, GPR, td);
-        else mm_jds_sum<LPR, CPL, false, VT, XT>(jp_s, dlim, col, val, Xr, k, j, r, ok, r_first, sub, GPR, td);
+        if (F64 || wide) mm_jds_sum<LPR, CPL, U, true, VT, XT>(jp_s, dlim, col, val, Xr, ld, k, j, r, ok, r_first, sub * D + dl, GPR * D, td);
+        else mm_jds_sum<LPR, CPL, U, false, VT, XT>(jp_s, dlim, col, val, Xr, ld, k, j, r, ok, r_first, sub * D + dl, GPR * D, td);
     } else {
-        if (F64 || wide) mm_jds_sum<LPR, CPL, true, VT, XT>(jp, dlim, col, val, Xr, k, j, r, ok, r_first, sub, GPR, td);
-        else mm_jds_sum<LPR, CPL, false, VT, XT>(jp, dlim, col, val, Xr, k, j, r, ok, r_first, sub, GPR, td);
+        if (F64 || wide) mm_jds_sum<LPR, CPL, U, true, VT, XT>(jp, dlim, col, val, Xr, ld, k, j, r, ok, r_first, sub * D + dl, GPR * D, td);
+        else mm_jds_sum<LPR, CPL, U, false, VT, XT>(jp, dlim, col, val, Xr, ld, k, j, r, ok, r_first, sub * D + dl, GPR * D, td);
     }
+    // the D groups of a row: fixed xor tree
+    if (SMALL)
+        for (int off = LPR * RPW; off < WAVE; off <<= 1)
+#pragma unroll
+            for (int t = 0; t < CPL; ++t) td[t] += __shfl_xor(td[t], off, WAVE);
     if (GPR > 1) {
 #pragma unroll
         for (int t = 0; t < CPL; ++t) part[g][t * LPR + j] = td[t];
         __syncthreads();
-        if (sub == 0 && ok) {
+        if (sub == 0 && dl == 0 && ok) {
             // the row's GPR partial sums sit in wavefronts rs*GPR .. rs*GPR+GPR-1, same lane group
             const int g0 = rs * GPR * GPW + gl;
 #pragma unroll
@@ -551,7 +587,7 @@ __global__ __launch_bounds__(NT) void spmm_jds_il_kernel(int32_t ndiag, const in
             }
         }
     }
-    if (sub == 0 && ok) {
+    if (sub == 0 && dl == 0 && ok) {
         const int32_t yi = symperm ? r : perm[r];
 #pragma unroll
         for (int t = 0; t < CPL; ++t)
@@ -581,13 +617,13 @@ template <int K2, typename VT, typename XT>
 __global__ __launch_bounds__(MM_BLK_THREADS) void spmm_blk_il_kernel(
     int32_t n, const int32_t *__restrict__ perm, int32_t C, const int64_t *__restrict__ slice_ptr,
     const int32_t *__restrict__ slice_nd, const int32_t *__restrict__ col, const VT *__restrict__ val,
-    const XT *__restrict__ Xr, int32_t k, XT *__restrict__ Y, int64_t ldy, const int32_t *__restrict__ recs,
+    const XT *__restrict__ Xr, int32_t ld, int32_t k, XT *__restrict__ Y, int64_t ldy, const int32_t *__restrict__ recs,
     double alpha, double beta)
 {
     constexpr int LPR = mm_jds_lpr<K2, XT>();
     constexpr int CPL = K2 / LPR;
     constexpr bool F64 = IsF64<VT>::value;
-    constexpr int U = CPL == 1 ? 4 : 2;     // diagonals per trip: 4 measured 5-14% faster at k <= 8, 2 at k = 32
+    constexpr int U = CPL <= 2 ? 4 : 2;     // diagonals per trip: 4 measured 5-14% faster up to k = 16, 2 at k = 32
     __shared__ double part[MM_BLK_WAVES][CPL][WAVE];
     // ranged plan (recs[0] >= 0): workgroup b runs on XCD b % 8 and takes
     // the (b / 8)-th record of that XCD's range (ranges of equal stored work,
@@ -630,6 +666,8 @@ __global__ __launch_bounds__(MM_BLK_THREADS) void spmm_blk_il_kernel(
     }
     const int32_t dA = (int32_t)((int64_t)p * nd / S), dB = (int32_t)((int64_t)(p + 1) * nd / S);
     double td[CPL];
+    int32_t cj[CPL];
+    mm_columns<LPR, CPL>(cj, k, j);
     auto walk = [&](auto acc_tag) {
         typedef decltype(acc_tag) acc_t;
         constexpr bool WD = sizeof(acc_t) == 8;
@@ -659,13 +697,12 @@ __global__ __launch_bounds__(MM_BLK_THREADS) void spmm_blk_il_kernel(
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int t = 0; t < CPL; ++t)
-                    xv[u][t] = (c[u] >= 0 && t * LPR + j < k) ? Xr[(int64_t)c[u] * k + t * LPR + j] : XT(0);
+                    xv[u][t] = Xr[(int64_t)max(c[u], 0) * ld + cj[t]];
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (c[u] >= 0) {
 #pragma unroll
-                    for (int t = 0; t < CPL; ++t) sacc[t] = Acc<WD>::mac(sacc[t], v[u], xv[u][t]);
-                }
+                for (int t = 0; t < CPL; ++t)
+                    sacc[t] = c[u] >= 0 ? Acc<WD>::mac(sacc[t], v[u], xv[u][t]) : sacc[t];
         }
         // the D groups of a row: fixed xor tree over the group index
         for (int off = LPR; off < LPR * D; off <<= 1)
@@ -774,19 +811,25 @@ static int64_t plan_mm_blk_words(int32_t n, int32_t C, int32_t n_slices, const i
     return longest * MM_BLK_XCDS;
 }
 
-static int k2_for(int32_t k)
+// Columns a kernel is built for: a power of two up to 8, then the next
+// multiple of 8 (of the 16 lanes per row of the FP64 CRS kernel): a lane's
+// column groups all hold a column that exists (with K2 the next power of two,
+// k = 20 as 32: windowed FP64 775 us against 743, banded 582 against 516).
+static int k2_for(int32_t k, int lpr = 8)
 {
+    if (k > 8) return (k + lpr - 1) / lpr * lpr;
     int K2 = 1;
-    while (K2 < k && K2 < MM_MAX_K2) K2 *= 2;
+    while (K2 < k) K2 *= 2;
     return K2;
 }
 
 // NG row groups per workgroup, NW wavefronts per workgroup: a class's rows
-// get GPR = 1, 2, ..., NW wavefronts each (a power of two), NG / GPR rows per
-// workgroup.
+// get GPR = 1, 2, ..., NW wavefronts each (a power of two), then D lane groups.
 static MmPlan plan_mm_jds(int32_t n, const int32_t *h_jd_ptr, int32_t ndiag, int NG, int NW)
 {
-    constexpr int64_t LT = 32;   // target diagonals per group
+    const bool small = n < MM_SMALL_ROWS;
+    const int64_t LT = small ? 16 : 32;                  // target diagonals per group
+    const int gpw = NG / NW, dmax = !small ? 1 : n < MM_TINY_ROWS ? gpw : std::max(1, gpw / 2);
     MmPlan P{};
     auto len_of = [&](int64_t row) -> int64_t {
         int32_t lo = 0, hi = ndiag;
@@ -797,17 +840,18 @@ static MmPlan plan_mm_jds(int32_t n, const int32_t *h_jd_ptr, int32_t ndiag, int
         }
         return lo;
     };
+    // groups per row: wavefronts first, then lane groups inside them
     auto gpr_of = [&](int64_t L) {
         int gpr = 1;
-        while (gpr < NW && gpr * LT < L) gpr *= 2;
+        while (gpr < NW * dmax && gpr * LT < L) gpr *= 2;
         return gpr;
     };
     int64_t row = 0, wgs = 0;
     int cls = 0;
-    while (row < n && cls < 8) {
+    while (row < n && cls < MM_CLASSES) {
         const int gpr = gpr_of(len_of(row));
         int64_t end = n;
-        if (cls < 7 && gpr > 1) {
+        if (cls < MM_CLASSES - 1 && gpr > 1) {
             // rows needing this many groups: length > (gpr/2)*LT; lengths never increase
             const int64_t lower = (int64_t)(gpr / 2) * LT;
             int64_t lo = row + 1, hi = n;
@@ -821,7 +865,9 @@ static MmPlan plan_mm_jds(int32_t n, const int32_t *h_jd_ptr, int32_t ndiag, int
         MmClass &K = P.c[cls++];
         K.row_start = (int32_t)row;
         K.row_end = (int32_t)end;
-        K.gpr = gpr;
+        K.gpr = std::min(gpr, NW);
+        K.log_d = 0;
+        while (K.gpr << K.log_d < gpr) ++K.log_d;
         K.len0 = (int32_t)len_of(row);
         wgs += ceil_div(end - row, NG / gpr);
         K.wg_end = (int32_t)wgs;
@@ -831,25 +877,50 @@ static MmPlan plan_mm_jds(int32_t n, const int32_t *h_jd_ptr, int32_t ndiag, int
     return P;
 }
 
+// Stride of the staged rows, in elements.  Rows of 33 to 127 bytes are padded
+// to 64 or 128, so that each lies in one 128-byte line: what the gathers fetch
+// is lines, and an unpadded row of 52 bytes (13 FP32 columns) is in two of
+// them for 40% of the entries, one of 104 bytes for 80% (JDS, 1 M power-law
+// rows, k = 13: FP32 482 to 435 us, FP64 631 to 480).  Shorter
+// rows rarely straddle (k = 3 and 5: within 3% either way), and above a line
+// the padding moves more than it saves (20 FP64 columns to 256 bytes: 611 to
+// 709 us).
+static int32_t mm_padded_ld(int32_t k, size_t elem)
+{
+    const size_t bytes = (size_t)k * elem;
+    const size_t row = bytes > 64 && bytes < 128 ? 128 : bytes > 32 && bytes < 64 ? 64 : bytes;
+    return (int32_t)(row / elem);
+}
+
+static size_t mm_ws_bytes(int32_t n_cols, int32_t ld, size_t elem)
+{
+    return align_up((size_t)n_cols * (size_t)ld * elem, 256) + 256;
+}
+
 // The row-major block the interleaved kernels read: X itself for k = 1,
-// otherwise Xr in the workspace, filled here.
+// otherwise Xr in the workspace, filled here.  A workspace of the unpadded
+// rows' size is taken, without the padding.
 template <typename T>
-static spmv_status stage(int64_t n, int32_t k, const void *X, int64_t ldx, void *ws, const void **Xr, hipStream_t s)
+static spmv_status stage(int32_t n, int32_t k, const void *X, int64_t ldx, void *ws, size_t ws_bytes, const void **Xr,
+                         int32_t *ld, hipStream_t s)
 {
     if (k == 1) {
         *Xr = X;
+        *ld = 1;
         return SPMV_OK;
     }
     *Xr = ws;
+    *ld = mm_padded_ld(k, sizeof(T));
+    if (ws_bytes < mm_ws_bytes(n, *ld, sizeof(T))) *ld = k;
     if (n == 0) return SPMV_OK;
     const int64_t rows = STAGE_ELEMS / k;              // 2 <= k <= MM_MAX_K2 = 64
-    stage_rowmajor_kernel<T><<<(unsigned)ceil_div(n, rows), STAGE_THREADS, 0, s>>>(n, k, (const T *)X, ldx, (T *)ws);
+    stage_rowmajor_kernel<T><<<(unsigned)ceil_div(n, rows), STAGE_THREADS, 0, s>>>(n, k, (const T *)X, ldx, (T *)ws, *ld);
     SPMV_CHECK_LAUNCH("spmm staging");
     return SPMV_OK;
 }
 
 template <int K2, typename VT, typename XT>
-static void launch_crs_il(const int32_t *row_ptr, const int32_t *col, const void *val, const void *Xr, int32_t k,
+static void launch_crs_il(const int32_t *row_ptr, const int32_t *col, const void *val, const void *Xr, int32_t ld, int32_t k,
                           void *Y, int64_t ldy, const int32_t *plan, int32_t nb, int32_t block_nnz, double alpha,
                           double beta, hipStream_t s)
 {
@@ -857,13 +928,14 @@ static void launch_crs_il(const int32_t *row_ptr, const int32_t *col, const void
                        (sizeof(XT) == 8 ? sizeof(int32_t) * ((size_t)mm_rp_lds(block_nnz) + 1) + mm_ytile_bytes<K2>()
                                         : 0);
     constexpr int NT = mm_crs_threads<K2, XT>();
-    spmm_crs_il_kernel<K2, NT, VT, XT><<<nb, NT, lds, s>>>(row_ptr, col, (const VT *)val, (const XT *)Xr, k,
-                                                          (XT *)Y, ldy, plan, block_nnz, alpha, beta);
+    if constexpr (K2 % mm_crs_lpr<K2, XT>() == 0)          // what k2_for gives
+        spmm_crs_il_kernel<K2, NT, VT, XT><<<nb, NT, lds, s>>>(row_ptr, col, (const VT *)val, (const XT *)Xr, ld, k,
+                                                              (XT *)Y, ldy, plan, block_nnz, alpha, beta);
 }
 
 template <int K2, typename VT, typename XT>
 static void launch_jds_il(int32_t n, const int32_t *h_jd_ptr, int32_t ndiag, const int32_t *jp, const int32_t *perm,
-                          int symperm, const int32_t *col, const void *val, const void *Xr, int32_t k, void *Y,
+                          int symperm, const int32_t *col, const void *val, const void *Xr, int32_t ld, int32_t k, void *Y,
                           int64_t ldy, double alpha, double beta, hipStream_t s)
 {
     constexpr int NT = MM_JDS_THREADS;
@@ -871,18 +943,23 @@ static void launch_jds_il(int32_t n, const int32_t *h_jd_ptr, int32_t ndiag, con
     if (P.ncls == 0) return;
     // room for the longest jd_ptr prefix a class stages (dlim + 1 <= min(ndiag + 1, MM_JP_LDS))
     const size_t lds = sizeof(int32_t) * (size_t)std::min<int64_t>((int64_t)ndiag + 1, MM_JP_LDS);
-    spmm_jds_il_kernel<K2, NT, VT, XT><<<(unsigned)P.c[P.ncls - 1].wg_end, NT, lds, s>>>(
-        ndiag, jp, perm, symperm, col, (const VT *)val, (const XT *)Xr, k, (XT *)Y, ldy, P, alpha, beta);
+    const unsigned grid = (unsigned)P.c[P.ncls - 1].wg_end;
+    if (n < MM_SMALL_ROWS)
+        spmm_jds_il_kernel<K2, true, NT, VT, XT><<<grid, NT, lds, s>>>(
+            ndiag, jp, perm, symperm, col, (const VT *)val, (const XT *)Xr, ld, k, (XT *)Y, ldy, P, alpha, beta);
+    else
+        spmm_jds_il_kernel<K2, false, NT, VT, XT><<<grid, NT, lds, s>>>(
+            ndiag, jp, perm, symperm, col, (const VT *)val, (const XT *)Xr, ld, k, (XT *)Y, ldy, P, alpha, beta);
 }
 
 template <int K2, typename VT, typename XT>
 static void launch_blk_il(int32_t n, const int32_t *perm, int32_t C, const int64_t *slice_ptr,
-                          const int32_t *slice_nd, const int32_t *col, const void *val, const void *Xr, int32_t k,
+                          const int32_t *slice_nd, const int32_t *col, const void *val, const void *Xr, int32_t ld, int32_t k,
                           void *Y, int64_t ldy, const int32_t *recs, int32_t grid, double alpha, double beta,
                           hipStream_t s)
 {
     spmm_blk_il_kernel<K2, VT, XT><<<(unsigned)grid, MM_BLK_THREADS, 0, s>>>(
-        n, perm, C, slice_ptr, slice_nd, col, (const VT *)val, (const XT *)Xr, k, (XT *)Y, ldy, recs, alpha, beta);
+        n, perm, C, slice_ptr, slice_nd, col, (const VT *)val, (const XT *)Xr, ld, k, (XT *)Y, ldy, recs, alpha, beta);
 }
 
 #define K2_SWITCH(K2VAR, CALL)          \
@@ -892,7 +969,11 @@ static void launch_blk_il(int32_t n, const int32_t *perm, int32_t C, const int64
     case 4: { constexpr int K2 = 4; CALL; } break;   \
     case 8: { constexpr int K2 = 8; CALL; } break;   \
     case 16: { constexpr int K2 = 16; CALL; } break; \
+    case 24: { constexpr int K2 = 24; CALL; } break; \
     case 32: { constexpr int K2 = 32; CALL; } break; \
+    case 40: { constexpr int K2 = 40; CALL; } break; \
+    case 48: { constexpr int K2 = 48; CALL; } break; \
+    case 56: { constexpr int K2 = 56; CALL; } break; \
     default: { constexpr int K2 = 64; CALL; } break; \
     }
 
@@ -905,7 +986,7 @@ extern "C" {
 size_t spmm_workspace_size(int32_t n_cols, int32_t k, spmv_dtype vec_dt)
 {
     if (n_cols < 0 || k < 0) return 0;
-    return align_up((size_t)n_cols * (size_t)k * dtype_size(vec_dt), 256) + 256;
+    return mm_ws_bytes(n_cols, k <= MM_MAX_K2 ? mm_padded_ld(k, dtype_size(vec_dt)) : k, dtype_size(vec_dt));
 }
 
 spmv_status spmm_crs(int32_t n_rows, int32_t n_cols, const int32_t *row_ptr, const int32_t *col_idx, const void *val,
@@ -925,16 +1006,17 @@ spmv_status spmm_crs(int32_t n_rows, int32_t n_cols, const int32_t *row_ptr, con
     if (!ws || k > MM_MAX_K2)
         return spmm_crs_colmajor(n_rows, n_cols, row_ptr, col_idx, val, val_dt, k, X, ldx, Y, ldy, vec_dt, alpha,
                                  beta, plan, n_blocks, s);
-    SPMV_REQUIRE(ws_bytes >= spmm_workspace_size(n_cols, k, vec_dt), "spmm_crs: workspace too small");
+    SPMV_REQUIRE(ws_bytes >= mm_ws_bytes(n_cols, k, dtype_size(vec_dt)), "spmm_crs: workspace too small");
     if (n_blocks == 0) return SPMV_OK;
     const void *Xr = nullptr;
-    spmv_status st = vec_dt == SPMV_F64 ? stage<double>(n_cols, k, X, ldx, ws, &Xr, s)
-                                        : stage<float>(n_cols, k, X, ldx, ws, &Xr, s);
+    int32_t ld = k;
+    spmv_status st = vec_dt == SPMV_F64 ? stage<double>(n_cols, k, X, ldx, ws, ws_bytes, &Xr, &ld, s)
+                                        : stage<float>(n_cols, k, X, ldx, ws, ws_bytes, &Xr, &ld, s);
     if (st != SPMV_OK) return st;
-    const int K2v = k2_for(k);
+    const int K2v = k2_for(k, vec_dt == SPMV_F64 ? 16 : 8);
 #define CRS_IL(VDT, VT, XDT, XT)                                                                              \
     if (val_dt == VDT && vec_dt == XDT) {                                                                     \
-        K2_SWITCH(K2v, (launch_crs_il<K2, VT, XT>(row_ptr, col_idx, val, Xr, k, Y, ldy, plan, n_blocks,        \
+        K2_SWITCH(K2v, (launch_crs_il<K2, VT, XT>(row_ptr, col_idx, val, Xr, ld, k, Y, ldy, plan, n_blocks,        \
                                                   block_nnz, alpha, beta, s)));                               \
         SPMV_CHECK_LAUNCH("spmm_crs");                                                                        \
         return SPMV_OK;                                                                                       \
@@ -968,16 +1050,17 @@ spmv_status spmm_jds(int32_t n, int32_t n_cols, const int32_t *perm, const int32
         return spmm_jds_colmajor(n, perm, jd_ptr, ndiag, jd_col, jd_val, val_dt, k, X, ldx, Y, ldy, vec_dt, alpha,
                                  beta, flags, s);
     SPMV_REQUIRE(h_jd_ptr, "spmm_jds: the interleaved path needs h_jd_ptr");
-    SPMV_REQUIRE(ws_bytes >= spmm_workspace_size(n_cols, k, vec_dt), "spmm_jds: workspace too small");
+    SPMV_REQUIRE(ws_bytes >= mm_ws_bytes(n_cols, k, dtype_size(vec_dt)), "spmm_jds: workspace too small");
     const void *Xr = nullptr;
-    spmv_status st = vec_dt == SPMV_F64 ? stage<double>(n_cols, k, X, ldx, ws, &Xr, s)
-                                        : stage<float>(n_cols, k, X, ldx, ws, &Xr, s);
+    int32_t ld = k;
+    spmv_status st = vec_dt == SPMV_F64 ? stage<double>(n_cols, k, X, ldx, ws, ws_bytes, &Xr, &ld, s)
+                                        : stage<float>(n_cols, k, X, ldx, ws, ws_bytes, &Xr, &ld, s);
     if (st != SPMV_OK) return st;
     const int K2v = k2_for(k);
     const int sym = (flags & SPMV_SYMPERM) ? 1 : 0;
 #define JDS_IL(VDT, VT, XDT, XT)                                                                                 \
     if (val_dt == VDT && vec_dt == XDT) {                                                                        \
-        K2_SWITCH(K2v, (launch_jds_il<K2, VT, XT>(n, h_jd_ptr, ndiag, jd_ptr, perm, sym, jd_col, jd_val, Xr, k, Y, \
+        K2_SWITCH(K2v, (launch_jds_il<K2, VT, XT>(n, h_jd_ptr, ndiag, jd_ptr, perm, sym, jd_col, jd_val, Xr, ld, k, Y, \
                                                   ldy, alpha, beta, s)));                                        \
         SPMV_CHECK_LAUNCH("spmm_jds");                                                                           \
         return SPMV_OK;                                                                                          \
@@ -1032,17 +1115,18 @@ spmv_status spmm_jds_blocked(int32_t n, int32_t n_cols, const int32_t *perm, int
     SPMV_REQUIRE(ldx >= n_cols && ldy >= n, "spmm_jds_blocked: leading dimension too small");
     SPMV_REQUIRE(n_slices == (int32_t)ceil_div(n, C), "spmm_jds_blocked: n_slices != ceil(n / C)");
     SPMV_REQUIRE(perm && slice_ptr && slice_nd && Y && plan && X, "spmm_jds_blocked: null pointer");
-    SPMV_REQUIRE(ws && ws_bytes >= spmm_workspace_size(n_cols, k, vec_dt), "spmm_jds_blocked: workspace too small");
+    SPMV_REQUIRE(ws && ws_bytes >= mm_ws_bytes(n_cols, k, dtype_size(vec_dt)), "spmm_jds_blocked: workspace too small");
     hipStream_t s = as_stream(stream);
     const void *Xr = nullptr;
-    spmv_status st = vec_dt == SPMV_F64 ? stage<double>(n_cols, k, X, ldx, ws, &Xr, s)
-                                        : stage<float>(n_cols, k, X, ldx, ws, &Xr, s);
+    int32_t ld = k;
+    spmv_status st = vec_dt == SPMV_F64 ? stage<double>(n_cols, k, X, ldx, ws, ws_bytes, &Xr, &ld, s)
+                                        : stage<float>(n_cols, k, X, ldx, ws, ws_bytes, &Xr, &ld, s);
     if (st != SPMV_OK) return st;
     if (grid == 0) return SPMV_OK;
     const int K2v = k2_for(k);
 #define BLK_IL(VDT, VT, XDT, XT)                                                                                 \
     if (val_dt == VDT && vec_dt == XDT) {                                                                        \
-        K2_SWITCH(K2v, (launch_blk_il<K2, VT, XT>(n, perm, C, slice_ptr, slice_nd, bl_col, bl_val, Xr, k, Y, ldy,  \
+        K2_SWITCH(K2v, (launch_blk_il<K2, VT, XT>(n, perm, C, slice_ptr, slice_nd, bl_col, bl_val, Xr, ld, k, Y, ldy,  \
                                                   plan, grid, alpha, beta, s)));                                 \
         SPMV_CHECK_LAUNCH("spmm_jds_blocked");                                                                   \
         return SPMV_OK;                                                                                          \
