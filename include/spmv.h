@@ -773,12 +773,14 @@ spmv_status spmv_crs_sym_staged(int32_t n, const int32_t *row_ptr, const int32_t
  * SPMV_BATCHED_PLAN_WORDS int32 per tile into the device array `plan`
  * (capacity plan_cap int32); *h_n_tiles returns the tile count; if the
  * capacity is too small returns SPMV_ERR_CAPACITY.  Synchronises.
- * spmv_batched runs all tiles in one persistent launch of n_workgroups
- * 256-lane workgroups (0 = 8 per compute unit; rounded to a multiple of 8):
- * each XCD walks one contiguous eighth of the table with a fixed wavefront
- * stride, so results are deterministic and the launch is capturable in a
- * HIP graph.
- * unroll: diagonals per trip (2, 4 or 8; 0 = 4). */
+ * spmv_batched runs all tiles in one persistent launch: each XCD walks one
+ * contiguous eighth of the table with a fixed stride, so results are
+ * deterministic and the launch is capturable in a HIP graph.
+ * unroll = 0 and n_workgroups = 0: the columns of x that a group of 8 tiles
+ * reads are staged in LDS (made for plans of 64 rows per wavefront; others
+ * run, slower than with unroll = 4).  Otherwise n_workgroups 256-lane
+ * workgroups (0 = 8 per compute unit; rounded to a multiple of 8) that take
+ * unroll (2, 4 or 8; 0 = 4) diagonals per trip and gather from x itself. */
 #define SPMV_BATCHED_PLAN_WORDS 12
 spmv_status spmv_batched_plan(int32_t n_mat, const int32_t *h_n_rows, const int32_t *h_C,
                               const int64_t *h_slice_base, const int64_t *h_row_base,
