@@ -191,4 +191,16 @@ __device__ __forceinline__ int64_t xcd_remap(int64_t bid, int64_t nblk)
     return xcd < r ? xcd * (q + 1) + local : r * (q + 1) + (xcd - r) * q + local;
 }
 
+// Workgroup index remapped so that each XCD takes RUN logical blocks in a row,
+// then the next XCD the next RUN: neighbouring rows share an L2 and the long
+// rows, which come first, still go to every XCD.
+template <int RUN>
+__device__ __forceinline__ int64_t xcd_runs(int64_t bid, int64_t nblk)
+{
+    constexpr int64_t NX = 8;
+    if (bid >= nblk / (NX * RUN) * (NX * RUN)) return bid;
+    const int64_t local = bid / NX;
+    return (local / RUN * NX + bid % NX) * RUN + local % RUN;
+}
+
 }  // namespace spmv

@@ -48,6 +48,7 @@ struct JdsPlan {
     JdsClass c[JDS_MAX_CLASSES];
     int32_t ncls;
     int32_t waves;      // wavefronts per workgroup (4, 8 or 16)
+    int32_t runs;       // 1: JDS_RUN workgroups in a row on each XCD
 };
 
 struct JdsArgs {
@@ -384,11 +385,26 @@ __global__ __launch_bounds__(JDS_THREADS) void jds_tiles_kernel(JdsArgs a, const
                                       part);
 }
 
+// Workgroups are dealt to the XCDs in turn; in runs of JDS_RUN, neighbouring
+// rows' gathers meet in one L2 (4 M banded rows, FP64: 481 to 443 us; 250 k
+// power-law rows, blocked, bf16: 47 to 39; runs of 2 half as much, of 16 and
+// 64 the long rows land unevenly: 2 M power-law rows, FP32: 243 at 4, 280 at
+// 64).  Short rows have too few gathers for it and stream better in turn
+// (7 entries, 3.4 M rows, FP64: 67.5 in turn, 69.0 in runs; 24 entries, 300 k
+// rows, bf16: 20.9 and 21.8; 25 entries, 6 M rows, FP64: 360 and 349).
+constexpr int JDS_RUN = 4;
+static int32_t jds_runs(int64_t n, int64_t longest, bool blocked)
+{
+    // blocked, small: 60 k power-law rows, FP64: 23.3 us in turn, 25.0 in runs
+    if (blocked && n < 100000) return 0;
+    return longest > 32 || (n >= 1000000 && longest > 16);
+}
+
 template <int FMT, int U, typename VT, typename XT>
 __global__ __launch_bounds__(JDS_THREADS) void jds_kernel(JdsArgs a, JdsPlan P)
 {
     __shared__ double part[JDS_WAVES][WAVE];
-    jds_body<FMT, U, VT, XT, XT>(a, P, blockIdx.x, part);
+    jds_body<FMT, U, VT, XT, XT>(a, P, P.runs ? xcd_runs<JDS_RUN>(blockIdx.x, gridDim.x) : blockIdx.x, part);
 }
 
 // Column-split JDS / blocked JDS: part k (the matrix restricted to the k-th
@@ -815,7 +831,7 @@ static spmv_status launch_jds_t(const JdsArgs &a, const JdsPlan &P, int unroll, 
 // order, since the sort is stable) is cut into 8 contiguous pieces, piece k
 // to XCD k, so each XCD's short rows come from one eighth of the original
 // rows; the remaining records (long rows, short runs) are dealt to the XCDs
-// for equal cost, longest first.  Each XCD walks its dealt records (in
+// for equal cost, in runs of neighbours, longest first.  Each XCD walks its dealt records (in
 // sorted order), then its pieces ordered by their place inside their runs
 // (all lengths side by side), so that it moves through its eighth of the
 // original rows once instead of once per length.
@@ -824,7 +840,7 @@ static spmv_status launch_jds_t(const JdsArgs &a, const JdsPlan &P, int unroll, 
 //   U: rows per unit (1 for JDS rows, C for slices); chunk: rows per split
 //     decision (64 for JDS, C for slices: a record never crosses a slice).
 // Runs of at least this many rows of one length are cut into 8 XCD pieces
-// (JDS on the power-law matrix: 512 and 1,024 rows 342 µs, 2,048 and 4,096
+// (JDS on the power-law matrix, others dealt singly: 512 and 1,024 rows 342 µs, 2,048 and 4,096
 // rows 348 µs, 16,384 rows 353 µs, the class plan 360 µs).
 constexpr int64_t TILE_LOCAL_MIN_RUN = 1024;
 
@@ -913,16 +929,25 @@ static void plan_tiles_local(int32_t n, int32_t U, int64_t n_units, F unit_len, 
         load[k] = 0;
         for (const Rec &r : pieces[k]) load[k] += r.cost;
     }
-    std::vector<int64_t> order(others.size());
-    for (size_t t = 0; t < order.size(); ++t) order[t] = (int64_t)t;
-    std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return others[a].cost > others[b].cost; });
+    // the others in runs of neighbouring records, whose gathers meet in one L2:
+    // one at a time, in fours and in sixteens 346, 341 and 333 us (2 M
+    // power-law rows, FP64), 114, 111 and 123 (700 k), 19.8, 16.9 and 17.9 (60
+    // k, blocked, FP32).  Where no row is long there are too few to share out
+    // evenly in runs (300 k rows of at most 26: 20.5 us, 23.4 in fours).
+    const size_t run = n_units == 0 || unit_len(0) <= 32 ? 1 : n >= 1500000 ? 16 : 4;
+    std::vector<double> cost(ceil_div(others.size(), run), 0.0);
+    std::vector<int64_t> order(cost.size());
+    for (size_t t = 0; t < others.size(); ++t) cost[t / run] += others[t].cost;
+    for (size_t g = 0; g < order.size(); ++g) order[g] = (int64_t)g;
+    std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return cost[a] > cost[b]; });
     std::vector<int64_t> dealt[8];
-    for (int64_t t : order) {
+    for (int64_t g : order) {
         int k = 0;
         for (int m = 1; m < 8; ++m)
             if (load[m] < load[k]) k = m;
-        dealt[k].push_back(t);
-        load[k] += others[t].cost;
+        for (size_t t = (size_t)g * run; t < std::min(others.size(), ((size_t)g + 1) * run); ++t)
+            dealt[k].push_back((int64_t)t);
+        load[k] += cost[g];
     }
     rec.clear();
     bounds[0] = 0;
@@ -1118,6 +1143,7 @@ spmv_status spmv_jds(int32_t n, const int32_t *perm, const int32_t *jd_ptr, cons
     a.symperm = (flags & SPMV_SYMPERM) ? 1 : 0;
     const JdsShape sh = jds_shape(false, false, false, n, ndiag, vec_dt == SPMV_F64);
     JdsPlan P = plan_jds(n, h_jd_ptr, ndiag, max_iters ? max_iters : sh.max_iters, -1, wg_waves ? wg_waves : sh.waves);
+    P.runs = jds_runs(n, ndiag, false);
     return launch_jds<FMT_JDS>(a, P, unroll ? unroll : sh.unroll, val_dt, vec_dt, as_stream(stream));
 }
 
@@ -1163,6 +1189,7 @@ spmv_status spmv_jds_blocked(int32_t n, const int32_t *perm, int32_t C, int32_t 
     const JdsShape sh = jds_shape(true, false, false, n, h_slice_nd[0], vec_dt == SPMV_F64);
     JdsPlan P = plan_blocked(n, C, h_slice_nd, max_iters ? max_iters : sh.max_iters, forced,
                              wg_waves ? wg_waves : sh.waves);
+    P.runs = jds_runs(n, h_slice_nd[0], true);
     return launch_jds<FMT_BLOCKED>(a, P, unroll ? unroll : sh.unroll, val_dt, vec_dt, as_stream(stream));
 }
 

@@ -522,7 +522,10 @@ __global__ __launch_bounds__(NT) void spmm_jds_il_kernel(int32_t ndiag, const in
     // wavefronts are in flight (2: 3-30% slower at 20 k rows)
     constexpr int U = SMALL ? 4 : 2;
     __shared__ double part[NG][K2];
-    const int64_t wg = blockIdx.x;
+    // workgroups in runs of 16 per XCD: neighbouring rows' lines meet in one L2
+    // (2 M power-law rows, 8 vectors, FP32: in turn 730 us, runs of 4 689, 16
+    // 674, 64 682, 256 808: the long rows then land unevenly)
+    const int64_t wg = xcd_runs<16>(blockIdx.x, gridDim.x);
     int ci = 0;
     while (ci < P.ncls - 1 && wg >= P.c[ci].wg_end) ++ci;
     const MmClass K = P.c[ci];
