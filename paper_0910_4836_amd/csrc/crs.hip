@@ -217,31 +217,77 @@ inline size_t crs_staged_lds_bytes(int32_t block_nnz, size_t val_bytes)
     return (size_t)ceil_div(block_nnz, CRS_LDS_ROUND) * CRS_LDS_ROUND * (val_bytes + sizeof(int32_t));
 }
 
-template <typename acc_t, bool F64, typename VT, typename XT>
+// One trip: U entries of the lane's row, k, k + G, ... below z.  A lane with
+// fewer gathers one entry again instead, its wavefront's first (FIRST: one
+// line for all such lanes) or its row's last.
+template <int U, bool FIRST, typename acc_t, bool F64, typename VT, typename XT>
+__device__ __forceinline__ acc_t crs_staged_trip(acc_t s, const VT *vs, const int32_t *cs, const XT *__restrict__ x,
+                                                 int32_t k, int32_t z, int G)
+{
+    const int32_t first = FIRST ? __builtin_amdgcn_readfirstlane(k) : 0;
+    int32_t c[U];
+    VT v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int32_t kk = FIRST ? (k + u * G < z ? k + u * G : first) : min(k + u * G, z - 1);
+        c[u] = cs[kk];
+        v[u] = vs[kk];
+    }
+    XT xv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) xv[u] = x[c[u]];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (k + u * G < z) s = Acc<F64>::mac(s, v[u], xv[u]);
+    return s;
+}
+
+template <bool FIRST, typename acc_t, bool F64, typename VT, typename XT>
 __device__ __forceinline__ acc_t crs_staged_row(const VT *vs, const int32_t *cs, const XT *__restrict__ x,
                                                 int32_t a, int32_t z, int l, int G)
 {
     acc_t s = 0;
     for (int32_t k = a + l; k < z; k += CRS_STAGE_U * G) {
-        int32_t c[CRS_STAGE_U];
-        VT v[CRS_STAGE_U];
+        if constexpr (FIRST) {
+            s = crs_staged_trip<CRS_STAGE_U, true, acc_t, F64>(s, vs, cs, x, k, z, G);
+        } else {
+            // written out: through crs_staged_trip it measured 2% slower
+            int32_t c[CRS_STAGE_U];
+            VT v[CRS_STAGE_U];
 #pragma unroll
-        for (int u = 0; u < CRS_STAGE_U; ++u) {
-            const int32_t kk = min(k + u * G, z - 1);
-            c[u] = cs[kk];
-            v[u] = vs[kk];
+            for (int u = 0; u < CRS_STAGE_U; ++u) {
+                const int32_t kk = min(k + u * G, z - 1);
+                c[u] = cs[kk];
+                v[u] = vs[kk];
+            }
+            XT xv[CRS_STAGE_U];
+#pragma unroll
+            for (int u = 0; u < CRS_STAGE_U; ++u) xv[u] = x[c[u]];
+#pragma unroll
+            for (int u = 0; u < CRS_STAGE_U; ++u)
+                if (k + u * G < z) s = Acc<F64>::mac(s, v[u], xv[u]);
         }
-        XT xv[CRS_STAGE_U];
-#pragma unroll
-        for (int u = 0; u < CRS_STAGE_U; ++u) xv[u] = x[c[u]];
-#pragma unroll
-        for (int u = 0; u < CRS_STAGE_U; ++u)
-            if (k + u * G < z) s = Acc<F64>::mac(s, v[u], xv[u]);
     }
     return s;
 }
 
-template <typename VT, typename XT>
+// A row of G lanes: in one trip of 5 or of 10 entries where no lane of the
+// wavefront has more (rows of 20 entries, 4 M, FP32: blocks of 1,024 entries,
+// 4 lanes per row, 412 us in trips of 8, 358 so; of 2,048, 2 lanes, 351 and
+// 314; rows of 13, 2 M, FP64, 2 lanes: 100 and 91).
+template <bool FIRST, typename acc_t, bool F64, typename VT, typename XT>
+__device__ __forceinline__ acc_t crs_staged_group_row(const VT *vs, const int32_t *cs, const XT *__restrict__ x,
+                                                      int32_t a, int32_t z, int l, int G)
+{
+    const int32_t k = a + l;
+    if (k >= z) return 0;
+    if (!__any(k + 10 * G < z) && __any(k + 8 * G < z))
+        return crs_staged_trip<10, FIRST, acc_t, F64>((acc_t)0, vs, cs, x, k, z, G);
+    if (!__any(k + 5 * G < z)) return crs_staged_trip<5, FIRST, acc_t, F64>((acc_t)0, vs, cs, x, k, z, G);
+    return crs_staged_row<FIRST, acc_t, F64>(vs, cs, x, k, z, 0, G);
+}
+
+template <bool FIRST, typename VT, typename XT>
 __global__ __launch_bounds__(CRS_THREADS) void crs_staged_kernel(const int32_t *__restrict__ row_ptr,
                                                                  const int32_t *__restrict__ col,
                                                                  const VT *__restrict__ val,
@@ -311,7 +357,7 @@ __global__ __launch_bounds__(CRS_THREADS) void crs_staged_kernel(const int32_t *
 
     if (nr <= CRS_THREADS) {
         acc_t s = 0;
-        if (g < nr) s = crs_staged_row<acc_t, F64>(vs, cs, x, lo[0] - e0, hi[0] - e0, l, G);
+        if (g < nr) s = crs_staged_group_row<FIRST, acc_t, F64>(vs, cs, x, lo[0] - e0, hi[0] - e0, l, G);
         s = group_sum(s, G);
         if (g < nr && l == 0) write_y(y, (int64_t)r0 + g, (double)s, alpha, beta);
         return;
@@ -320,13 +366,13 @@ __global__ __launch_bounds__(CRS_THREADS) void crs_staged_kernel(const int32_t *
     for (int j = 0; j < MAXJ; ++j) {
         const int32_t q = t + j * CRS_THREADS;
         if (q < nr) {
-            const acc_t s = crs_staged_row<acc_t, F64>(vs, cs, x, lo[j] - e0, hi[j] - e0, 0, 1);
+            const acc_t s = crs_staged_row<FIRST, acc_t, F64>(vs, cs, x, lo[j] - e0, hi[j] - e0, 0, 1);
             write_y(y, (int64_t)r0 + q, (double)s, alpha, beta);
         }
     }
     // rows past 2048 (a caller's plan may hold more rows than the planner's)
     for (int32_t q = t + MAXJ * CRS_THREADS; q < nr; q += CRS_THREADS) {
-        const acc_t s = crs_staged_row<acc_t, F64>(vs, cs, x, row_ptr[r0 + q] - e0, row_ptr[r0 + q + 1] - e0, 0, 1);
+        const acc_t s = crs_staged_row<FIRST, acc_t, F64>(vs, cs, x, row_ptr[r0 + q] - e0, row_ptr[r0 + q + 1] - e0, 0, 1);
         write_y(y, (int64_t)r0 + q, (double)s, alpha, beta);
     }
 }
@@ -798,8 +844,17 @@ static spmv_status launch_crs_staged(const int32_t *row_ptr, const int32_t *col,
 {
     if (n_blocks == 0) return SPMV_OK;
     const int32_t cap = (int32_t)(ceil_div(block_nnz, CRS_LDS_ROUND) * CRS_LDS_ROUND);
-    crs_staged_kernel<VT, XT><<<n_blocks, CRS_THREADS, crs_staged_lds_bytes(block_nnz, sizeof(VT)), s>>>(
-        row_ptr, col, (const VT *)val, (const XT *)x, (XT *)y, plan, cap, alpha, beta);
+    // blocks of up to 1,024 entries give a row more lanes, of which more run
+    // out: their spare gathers then cost most (banded, FP64: 457 us with the
+    // row's last entry, 441 with the wavefront's first).  Larger blocks have
+    // few, and there the choice costs (rows of 13, FP64, 2,048: 94 and 100 us)
+    const size_t lds = crs_staged_lds_bytes(block_nnz, sizeof(VT));
+    if (block_nnz <= 1024)
+        crs_staged_kernel<true, VT, XT><<<n_blocks, CRS_THREADS, lds, s>>>(
+            row_ptr, col, (const VT *)val, (const XT *)x, (XT *)y, plan, cap, alpha, beta);
+    else
+        crs_staged_kernel<false, VT, XT><<<n_blocks, CRS_THREADS, lds, s>>>(
+            row_ptr, col, (const VT *)val, (const XT *)x, (XT *)y, plan, cap, alpha, beta);
     SPMV_CHECK_LAUNCH("spmv_crs_staged");
     return SPMV_OK;
 }
