@@ -406,17 +406,32 @@ def _out_vec(y, n, x, beta, n_cols):
     return y
 
 
+# The staged kernel without being asked for: blocks of 1,024 entries whose rows
+# are short and get at least four lanes each (16 entries per row on average).
+# Against the plain kernel 1.00 to 1.35 times as fast (banded rows of 20, 4 M:
+# FP32 439 and 356 us, FP64 544 and 442; rows of 5 to 40, 300 k: 41 and 36;
+# diagonals, 1 M, FP64: 73 and 69).  Fewer entries per row and it is 0.9 to 1.1
+# (7: FP64 66 and 69 us; 13: FP32 114 and 120, FP64 191 and 172); power-law
+# rows: FP64 252 and 286.
+CRS_STAGED_LONGEST, CRS_STAGED_MEAN = 64, 16
+
+
+def _crs_staged(A: CSR) -> bool:
+    return A.staged or (0 < A.longest <= CRS_STAGED_LONGEST and A.block_nnz in (0, 1024)
+                        and A.nnz >= CRS_STAGED_MEAN * A.n_rows)
+
+
 def spmv_crs(A: CSR, x: torch.Tensor, y: Optional[torch.Tensor] = None, alpha: float = 1.0, beta: float = 0.0,
              use_plan: bool = True) -> torch.Tensor:
     """y = alpha*A x + beta*y with the CRS kernels (spmv_crs; spmv_crs_staged
-    when A.staged is set and the plan is used)."""
+    when the plan is used and A.staged is set or its rows favour it)."""
     y = _out_vec(y, A.n_rows, x, beta, A.n_cols)
     if use_plan and A.plan is None:
         spmv_crs_plan(A)
     plan = A.plan if use_plan else None
-    call("spmv_crs_staged" if (use_plan and A.staged) else "spmv_crs", A.n_rows, A.n_cols, _p(A.row_ptr), _p(A.col_idx), _p(A.val), dtype_code(A.val.dtype), _p(x),
-         _p(y), dtype_code(x.dtype), float(alpha), float(beta), _p(plan), A.n_blocks if use_plan else 0,
-         A.block_nnz if use_plan else 0, _stream())
+    call("spmv_crs_staged" if use_plan and _crs_staged(A) else "spmv_crs", A.n_rows, A.n_cols, _p(A.row_ptr),
+         _p(A.col_idx), _p(A.val), dtype_code(A.val.dtype), _p(x), _p(y), dtype_code(x.dtype), float(alpha),
+         float(beta), _p(plan), A.n_blocks if use_plan else 0, A.block_nnz if use_plan else 0, _stream())
     return y
 
 

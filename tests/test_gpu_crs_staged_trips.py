@@ -36,3 +36,24 @@ def test_row_lengths(length, block_nnz, mixed):
     err = oracle.rel_err(sp.spmv_crs(Af, to_dev(xf)).cpu().numpy(), oracle.spmv_crs(R, xf.astype(np.float64)),
                          oracle.row_absdot(R, xf.astype(np.float64)))
     assert np.all(err <= (R.row_lengths() + 1) * 2.0 ** -24 * 1.001)
+
+
+@pytest.mark.parametrize("length,longest,block_nnz,staged", [
+    (16, 16, 0, True), (15, 64, 0, False), (17, 64, 0, True), (17, 65, 0, False), (20, 20, 1024, True),
+    (20, 20, 512, False), (20, 20, 2048, False)])
+def test_kernel_follows_from_the_rows(monkeypatch, length, longest, block_nnz, staged):
+    from paper_0910_4836_amd import spmv as module
+    rng = np.random.default_rng(length + longest)
+    n = 2000
+    lengths = np.full(n, length)
+    lengths[5] = longest
+    r = np.repeat(np.arange(n), lengths).astype(np.int32)
+    c = np.concatenate([rng.choice(n, k, replace=False) for k in lengths]).astype(np.int32)
+    v, x = rng.standard_normal(r.size), rng.uniform(-1, 1, n)
+    A = sp.spmv_crs_plan(gpu_csr(sp, r, c, v, n, n), block_nnz)
+    names, call = [], module.call
+    monkeypatch.setattr(module, "call", lambda name, *args: (names.append(name), call(name, *args))[1])
+    y = sp.spmv_crs(A, to_dev(x))
+    assert names == ["spmv_crs_staged" if staged else "spmv_crs"]
+    R = oracle.csr_from_coo(n, n, r, c, v)
+    assert max_err(y, oracle.spmv_crs(R, x), oracle.row_absdot(R, x)) <= FP64_TOL
