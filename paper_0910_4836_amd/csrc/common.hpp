@@ -192,15 +192,16 @@ __device__ __forceinline__ int64_t xcd_remap(int64_t bid, int64_t nblk)
 }
 
 // Workgroup index remapped so that each XCD takes RUN logical blocks in a row,
-// then the next XCD the next RUN: neighbouring rows share an L2 and the long
-// rows, which come first, still go to every XCD.
-template <int RUN>
+// then the next XCD the next RUN: neighbouring rows share an L2, and the long
+// rows, which come first, still go to every XCD.  TURN: the XCDs to and fro, so
+// that in long runs the first does not get the longest rows of every round.
+template <int RUN, bool TURN = false>
 __device__ __forceinline__ int64_t xcd_runs(int64_t bid, int64_t nblk)
 {
     constexpr int64_t NX = 8;
     if (bid >= nblk / (NX * RUN) * (NX * RUN)) return bid;
-    const int64_t local = bid / NX;
-    return (local / RUN * NX + bid % NX) * RUN + local % RUN;
+    const int64_t local = bid / NX, round = local / RUN, xcd = bid % NX;
+    return (round * NX + (TURN && (round & 1) ? NX - 1 - xcd : xcd)) * RUN + local % RUN;
 }
 
 }  // namespace spmv

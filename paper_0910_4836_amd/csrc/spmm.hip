@@ -439,8 +439,15 @@ __global__ __launch_bounds__(NT) void spmm_crs_il_kernel(const int32_t *__restri
 // k = 8, FP32: 734 us at D = 1, 861 with D <= 4 and no class split finer than
 // 32 diagonals).  Between MM_TINY_ROWS and MM_SMALL_ROWS half as many groups
 // (250 k rows, k = 8: D <= 4 106 us, D <= 8 124, D = 1 190).
+// Where no row is long, it pays for few vectors or very few rows only (74 k
+// rows of 5 to 40, FP32: 2 vectors 19 and 21 us, 3 24 and 21, 6 31 and 34, 40
+// vectors 86 and 100; 20 k rows, 12 vectors: 19.5 to 16.3).
 constexpr int64_t MM_SMALL_ROWS = 300000;
 constexpr int64_t MM_TINY_ROWS = 150000;
+static bool mm_small(int64_t n, int64_t longest, int k)
+{
+    return n < MM_SMALL_ROWS && (longest > 64 || k == 3 || k == 4 || n < 60000);
+}
 struct MmClass {
     int32_t wg_end, row_start, row_end, gpr;
     int32_t log_d;      // log2 of the lane groups per row inside a wavefront
@@ -450,6 +457,7 @@ constexpr int MM_CLASSES = 10;             // groups per row: 1, 2, ..., 8 wavef
 struct MmPlan {
     MmClass c[MM_CLASSES];
     int32_t ncls;
+    int32_t short_runs;     // workgroups go to the XCDs in runs of 2, not 16
 };
 
 // One lane's share of a JDS row for the interleaved multi-vector kernel:
@@ -519,13 +527,16 @@ __global__ __launch_bounds__(NT) void spmm_jds_il_kernel(int32_t ndiag, const in
     constexpr int GPW = WAVE / LPR;            // rows per wavefront
     constexpr bool F64 = IsF64<VT>::value;
     // diagonals per trip: two at size (4: 1-3% slower, 8 more), four where few
-    // wavefronts are in flight (2: 3-30% slower at 20 k rows)
-    constexpr int U = SMALL ? 4 : 2;
+    // wavefronts are in flight (250 k power-law rows, 40 vectors, FP64: 349 us
+    // with 2, 314), until they take too many registers (64, FP32: 282 with 2, 316)
+    constexpr int U = SMALL && CPL < 8 ? 4 : 2;
     __shared__ double part[NG][K2];
     // workgroups in runs of 16 per XCD: neighbouring rows' lines meet in one L2
     // (2 M power-law rows, 8 vectors, FP32: in turn 730 us, runs of 4 689, 16
-    // 674, 64 682, 256 808: the long rows then land unevenly)
-    const int64_t wg = xcd_runs<16>(blockIdx.x, gridDim.x);
+    // 674, 64 682, 256 808: the long rows then land unevenly).  Few rows, none
+    // long, are too few for runs of 16 (74 k rows of 5 to 40, 32 vectors, FP32:
+    // in turn 64 us, runs of 2 59, 4 67, 16 80).
+    const int64_t wg = P.short_runs ? xcd_runs<2, true>(blockIdx.x, gridDim.x) : xcd_runs<16, true>(blockIdx.x, gridDim.x);
     int ci = 0;
     while (ci < P.ncls - 1 && wg >= P.c[ci].wg_end) ++ci;
     const MmClass K = P.c[ci];
@@ -828,9 +839,8 @@ static int k2_for(int32_t k, int lpr = 8)
 
 // NG row groups per workgroup, NW wavefronts per workgroup: a class's rows
 // get GPR = 1, 2, ..., NW wavefronts each (a power of two), then D lane groups.
-static MmPlan plan_mm_jds(int32_t n, const int32_t *h_jd_ptr, int32_t ndiag, int NG, int NW)
+static MmPlan plan_mm_jds(int32_t n, const int32_t *h_jd_ptr, int32_t ndiag, bool small, int NG, int NW)
 {
-    const bool small = n < MM_SMALL_ROWS;
     const int64_t LT = small ? 16 : 32;                  // target diagonals per group
     const int gpw = NG / NW, dmax = !small ? 1 : n < MM_TINY_ROWS ? gpw : std::max(1, gpw / 2);
     MmPlan P{};
@@ -877,21 +887,23 @@ static MmPlan plan_mm_jds(int32_t n, const int32_t *h_jd_ptr, int32_t ndiag, int
         row = end;
     }
     P.ncls = cls;
+    P.short_runs = n < MM_TINY_ROWS && ndiag <= 64;
     return P;
 }
 
-// Stride of the staged rows, in elements.  Rows of 33 to 127 bytes are padded
+// Stride of the staged rows, in elements.  Rows of 41 to 127 bytes are padded
 // to 64 or 128, so that each lies in one 128-byte line: what the gathers fetch
 // is lines, and an unpadded row of 52 bytes (13 FP32 columns) is in two of
 // them for 40% of the entries, one of 104 bytes for 80% (JDS, 1 M power-law
 // rows, k = 13: FP32 482 to 435 us, FP64 631 to 480).  Shorter
-// rows rarely straddle (k = 3 and 5: within 3% either way), and above a line
+// rows straddle less than the padding adds (k = 9, FP32, 36 bytes: 1 M
+// power-law rows 403 to 393 us, 80 k banded rows 34.7 and 37.5), and above a line
 // the padding moves more than it saves (20 FP64 columns to 256 bytes: 611 to
 // 709 us).
 static int32_t mm_padded_ld(int32_t k, size_t elem)
 {
     const size_t bytes = (size_t)k * elem;
-    const size_t row = bytes > 64 && bytes < 128 ? 128 : bytes > 32 && bytes < 64 ? 64 : bytes;
+    const size_t row = bytes > 64 && bytes < 128 ? 128 : bytes > 40 && bytes < 64 ? 64 : bytes;
     return (int32_t)(row / elem);
 }
 
@@ -942,12 +954,13 @@ static void launch_jds_il(int32_t n, const int32_t *h_jd_ptr, int32_t ndiag, con
                           int64_t ldy, double alpha, double beta, hipStream_t s)
 {
     constexpr int NT = MM_JDS_THREADS;
-    const MmPlan P = plan_mm_jds(n, h_jd_ptr, ndiag, NT / mm_jds_lpr<K2, XT>(), NT / WAVE);
+    const bool small = mm_small(n, ndiag, k);
+    const MmPlan P = plan_mm_jds(n, h_jd_ptr, ndiag, small, NT / mm_jds_lpr<K2, XT>(), NT / WAVE);
     if (P.ncls == 0) return;
     // room for the longest jd_ptr prefix a class stages (dlim + 1 <= min(ndiag + 1, MM_JP_LDS))
     const size_t lds = sizeof(int32_t) * (size_t)std::min<int64_t>((int64_t)ndiag + 1, MM_JP_LDS);
     const unsigned grid = (unsigned)P.c[P.ncls - 1].wg_end;
-    if (n < MM_SMALL_ROWS)
+    if (small)
         spmm_jds_il_kernel<K2, true, NT, VT, XT><<<grid, NT, lds, s>>>(
             ndiag, jp, perm, symperm, col, (const VT *)val, (const XT *)Xr, ld, k, (XT *)Y, ldy, P, alpha, beta);
     else

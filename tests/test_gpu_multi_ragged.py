@@ -54,3 +54,21 @@ def test_jds_launch_changes_with_the_row_count(n, k):
     got, want = to_np(sp.spmm_jds(J, Xd)), oracle.spmm_crs(R, X)
     for j in range(k):
         assert oracle.rel_err(got[:, j], want[:, j], oracle.row_absdot(R, X[:, j])).max() <= FP64_TOL
+
+
+@pytest.mark.parametrize("k", [4, 5])
+@pytest.mark.parametrize("n,longest", [(59_999, 20), (60_000, 20), (60_000, 64), (60_000, 65), (149_999, 20),
+                                       (150_000, 20)])
+def test_jds_launch_changes_with_the_longest_row_and_vector_count(n, longest, k):
+    rng = np.random.default_rng(n + k)
+    r = np.concatenate([np.arange(n), np.full(longest - 1, 7)]).astype(np.int32)
+    c = rng.integers(0, n, r.size).astype(np.int32)
+    c[n:], c[7] = np.arange(1, longest), 0                   # row 7: `longest` distinct columns
+    v = rng.standard_normal(r.size)
+    R = oracle.csr_from_coo(n, n, r, c, v)
+    J = sp.jds_from_csr(gpu_csr(sp, r, c, v, n, n))
+    Xd = block(rng, n, k, torch.float64)
+    X = to_np(Xd)
+    got, want = to_np(sp.spmm_jds(J, Xd)), oracle.spmm_crs(R, X)
+    for j in range(k):
+        assert oracle.rel_err(got[:, j], want[:, j], oracle.row_absdot(R, X[:, j])).max() <= FP64_TOL
