@@ -108,7 +108,7 @@ __global__ __launch_bounds__(STAGE_THREADS) void stage_rowmajor_kernel(int64_t n
 // line) and never writes the sum.  A guard instead of the clamp puts every
 // gather behind a branch of its own, which the scheduler does not move loads
 // across (CRS, 2 M power-law rows, k = 8, FP32: 956 us with the guard, 578
-// with the clamp; windowed, k = 13: 833 and 735).  The JDS kernel keeps its
+// with the clamp; windowed, k = 13: 833 and 760).  The JDS kernel keeps its
 // guard, which the entry's own mask needs anyway (no difference measured).
 template <int LPR, int CPL>
 __device__ __forceinline__ void mm_columns(int32_t (&cj)[CPL], int32_t k, int j)
@@ -627,7 +627,13 @@ constexpr int MM_BLK_DIAGS = 32;           // target diagonals per lane
 constexpr int MM_BLK_MAX_D = 8;
 constexpr int MM_BLK_XCDS = 8;             // MI355X: workgroup b runs on XCD b % 8
 
-template <int K2, typename VT, typename XT>
+// U: diagonals per trip.  4 with one column per lane (5-14% faster than 2), 2
+// with more (32 vectors: 4 is slower), but 4 for two columns below
+// MM_BLK_SMALL_ROWS rows (86 k power-law rows, 13 vectors, FP32: 80 us with 2,
+// 65 with 4; 640 k uniform rows, 10 vectors: 320 and 351).
+constexpr int64_t MM_BLK_SMALL_ROWS = 150000;
+
+template <int K2, int U, typename VT, typename XT>
 __global__ __launch_bounds__(MM_BLK_THREADS) void spmm_blk_il_kernel(
     int32_t n, const int32_t *__restrict__ perm, int32_t C, const int64_t *__restrict__ slice_ptr,
     const int32_t *__restrict__ slice_nd, const int32_t *__restrict__ col, const VT *__restrict__ val,
@@ -637,7 +643,6 @@ __global__ __launch_bounds__(MM_BLK_THREADS) void spmm_blk_il_kernel(
     constexpr int LPR = mm_jds_lpr<K2, XT>();
     constexpr int CPL = K2 / LPR;
     constexpr bool F64 = IsF64<VT>::value;
-    constexpr int U = CPL <= 2 ? 4 : 2;     // diagonals per trip: 4 measured 5-14% faster up to k = 16, 2 at k = 32
     __shared__ double part[MM_BLK_WAVES][CPL][WAVE];
     // ranged plan (recs[0] >= 0): workgroup b runs on XCD b % 8 and takes
     // the (b / 8)-th record of that XCD's range (ranges of equal stored work,
@@ -711,7 +716,12 @@ __global__ __launch_bounds__(MM_BLK_THREADS) void spmm_blk_il_kernel(
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int t = 0; t < CPL; ++t)
-                    xv[u][t] = Xr[(int64_t)max(c[u], 0) * ld + cj[t]];
+                    // with one column per lane the mask is the only branch, and what it
+                    // skips is worth it (310 k uniform rows, 8 vectors, FP64: 155 and
+                    // 162 us); with more, a branch per gather costs more (13 vectors,
+                    // 1 M banded rows, FP32: 252 and 327)
+                    xv[u][t] = CPL == 1 ? (c[u] >= 0 ? Xr[(int64_t)c[u] * ld + cj[t]] : XT(0))
+                                        : Xr[(int64_t)max(c[u], 0) * ld + cj[t]];
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -974,8 +984,17 @@ static void launch_blk_il(int32_t n, const int32_t *perm, int32_t C, const int64
                           void *Y, int64_t ldy, const int32_t *recs, int32_t grid, double alpha, double beta,
                           hipStream_t s)
 {
-    spmm_blk_il_kernel<K2, VT, XT><<<(unsigned)grid, MM_BLK_THREADS, 0, s>>>(
-        n, perm, C, slice_ptr, slice_nd, col, (const VT *)val, (const XT *)Xr, ld, k, (XT *)Y, ldy, recs, alpha, beta);
+    constexpr int CPL = K2 / mm_jds_lpr<K2, XT>();
+#define BLK_IL_LAUNCH(U)                                                                                           \
+    spmm_blk_il_kernel<K2, U, VT, XT><<<(unsigned)grid, MM_BLK_THREADS, 0, s>>>(                                   \
+        n, perm, C, slice_ptr, slice_nd, col, (const VT *)val, (const XT *)Xr, ld, k, (XT *)Y, ldy, recs, alpha, beta)
+    if constexpr (CPL == 2) {
+        if (n < MM_BLK_SMALL_ROWS) BLK_IL_LAUNCH(4);
+        else BLK_IL_LAUNCH(2);
+    } else {
+        BLK_IL_LAUNCH(CPL == 1 ? 4 : 2);
+    }
+#undef BLK_IL_LAUNCH
 }
 
 #define K2_SWITCH(K2VAR, CALL)          \

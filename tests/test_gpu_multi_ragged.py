@@ -72,3 +72,18 @@ def test_jds_launch_changes_with_the_longest_row_and_vector_count(n, longest, k)
     got, want = to_np(sp.spmm_jds(J, Xd)), oracle.spmm_crs(R, X)
     for j in range(k):
         assert oracle.rel_err(got[:, j], want[:, j], oracle.row_absdot(R, X[:, j])).max() <= FP64_TOL
+
+
+@pytest.mark.parametrize("n", [149_999, 150_000])
+def test_windowed_launch_changes_with_the_row_count(n):
+    rng = np.random.default_rng(n)
+    r = np.concatenate([np.arange(n), np.full(300, 11), np.full(70, n - 2)]).astype(np.int32)
+    c = rng.integers(0, n, r.size).astype(np.int32)
+    v = rng.standard_normal(r.size)
+    R = oracle.csr_from_coo(n, n, r, c, v)
+    B = sp.jds_blocked_windowed_from_csr(gpu_csr(sp, r, c, v, n, n), 64, 4096)
+    Xd = block(rng, n, 13, torch.float64)
+    X = to_np(Xd)
+    got, want = to_np(sp.spmm_jds_blocked(B, Xd)), oracle.spmm_crs(R, X)
+    for j in range(13):
+        assert oracle.rel_err(got[:, j], want[:, j], oracle.row_absdot(R, X[:, j])).max() <= FP64_TOL
