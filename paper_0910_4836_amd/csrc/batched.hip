@@ -121,7 +121,7 @@ __global__ __launch_bounds__(B_THREADS) void batched_kernel(int64_t n_tiles, con
 //
 // What bounds the plain form is the L2's rate of lines: every gathered x is a
 // 128-byte line of its own (128 matrices of 1,000 to 200,000 rows, 91 M
-// entries: 573 us, 24 TB/s out of the L2s, against 0.73 GB of entries).  Here
+// entries: 573 us, 20 TB/s out of the L2s, against 0.73 GB of entries).  Here
 // the x that a group of tiles reads, the columns from its smallest to its
 // largest, passes through LDS once per group, in pieces of 40 KB (the next on
 // its way, by direct loads, while one is read) or 80 KB where that holds all
