@@ -188,7 +188,8 @@ class ChebyshevLoss(torch.autograd.Function):
         n = x.numel()
         # adjoint states bar[k]; only three are live at a time
         bar = {K: S.spmv_axpby(2.0 * scale, y_last, 0.0, torch.empty_like(y_last))}
-        dvals = torch.empty(op.nnz, dtype=vals.dtype, device=vals.device)
+        # in the vectors' type, which the products compute in, rounded to the values' at the end
+        dvals = torch.empty(op.nnz, dtype=x.dtype, device=vals.device)
         first_dval = True
 
         def get_bar(k):
@@ -229,6 +230,8 @@ class ChebyshevLoss(torch.autograd.Function):
                 op.grad_vals_sum(pairs, dvals, beta=0.0 if first_dval else 1.0)
                 first_dval = False
         dx = bar.pop(0)
+        if dvals.dtype != vals.dtype:
+            dvals = S.spmv_convert_values(dvals, vals.dtype)
         return dvals, dx, None, None, None
 
 

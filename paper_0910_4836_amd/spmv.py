@@ -650,13 +650,35 @@ def spmv_dot_noalloc(x: torch.Tensor, y: torch.Tensor, out: torch.Tensor) -> tor
     return out
 
 
-def spmv_grad_vals_jds(J: JDS, g: torch.Tensor, x: torch.Tensor, out: Optional[torch.Tensor] = None,
-                       alpha: float = 1.0, beta: float = 0.0) -> torch.Tensor:
-    """dval[e] = alpha*g[row_e]*x[col_e] + beta*dval[e] over the JDS entries."""
+def _grad_out(J: JDS, pairs, out: Optional[torch.Tensor], beta: float) -> torch.Tensor:
+    """Checks the vectors (g, x) of value gradients and out, all of one dtype,
+    and returns out (new if None).  The kernels read J.n and J.n_cols elements
+    and write J.nnz without bounds checks."""
+    dt = pairs[0][0].dtype
+    if dt not in _VEC_DTYPES:
+        raise TypeError(f"g and x must be float64 or float32, got {dt}")
+    for g, x in pairs:
+        if g.dtype != dt or x.dtype != dt or g.numel() < J.n or x.numel() < J.n_cols:
+            raise ValueError(f"g and x must be {dt} vectors of {J.n} and {J.n_cols} elements")
+    if out is not None:
+        if out.dtype != dt:
+            raise ValueError(f"out is {out.dtype} but g and x are {dt}; the gradient takes their dtype")
+        if out.numel() < J.nnz:
+            raise ValueError(f"out has {out.numel()} elements, the matrix has {J.nnz} entries")
+    for g, x in pairs:
+        _check_dev(g, x)
     if out is None:
         if beta != 0.0:
             raise ValueError("beta != 0 needs out")
-        out = torch.empty(J.nnz, dtype=g.dtype, device=g.device)
+        return torch.empty(J.nnz, dtype=dt, device=pairs[0][0].device)
+    _check_dev(out)
+    return out
+
+
+def spmv_grad_vals_jds(J: JDS, g: torch.Tensor, x: torch.Tensor, out: Optional[torch.Tensor] = None,
+                       alpha: float = 1.0, beta: float = 0.0) -> torch.Tensor:
+    """dval[e] = alpha*g[row_e]*x[col_e] + beta*dval[e] over the JDS entries."""
+    out = _grad_out(J, [(g, x)], out, beta)
     call("spmv_grad_vals_jds", J.n, _p(J.perm), _p(J.jd_ptr), _h_i32(J.h_jd_ptr), J.ndiag, J.nnz, _p(J.jd_col),
          _p(g), _p(x), _p(out), dtype_code(g.dtype), float(alpha), float(beta), J.flags, _stream())
     return out
@@ -667,14 +689,7 @@ def spmv_grad_vals_jds_sum(J: JDS, pairs, out: Optional[torch.Tensor] = None, be
     GRAD_MAX_PAIRS pairs (alpha, g, x), added in order: the calls of
     spmv_grad_vals_jds one after the other, in one pass over the entries."""
     g0 = pairs[0][1]
-    for _, g, x in pairs:
-        _check_dev(g, x)
-        if g.dtype != g0.dtype or x.dtype != g0.dtype or g.numel() < J.n or x.numel() < J.n_cols:
-            raise ValueError(f"g and x must be {g0.dtype} vectors of {J.n} and {J.n_cols} elements")
-    if out is None:
-        if beta != 0.0:
-            raise ValueError("beta != 0 needs out")
-        out = torch.empty(J.nnz, dtype=g0.dtype, device=g0.device)
+    out = _grad_out(J, [(g, x) for _, g, x in pairs], out, beta)
     m, dt = len(pairs), dtype_code(g0.dtype)
     tiles, nt, h_plan = spmv_jds_tiles(J)
     ws = _ws(_lib.load().spmv_grad_vals_jds_sum_workspace_size(J.n_cols, m, dt), g0.device)
