@@ -155,7 +155,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void jt_table_kernel(const int32_t *_
     for (int j = 0; j < SCAN_ITEMS; ++j) {
         const int32_t k = (int32_t)threadIdx.x * SCAN_ITEMS + j;
         v[j] = 0;
-        if (k < g.K) {
+        if (k < g.K && (int64_t)(k << g.q) * JT_DIAGS < ndiag) {       // jp ends with entry ndiag
             const int64_t reach = diag_len(jp, (k << g.q) * JT_DIAGS);
             const int64_t sets = C == 0 ? (min((int64_t)cut, reach) + JT_ROWS - 1) / JT_ROWS
                                         : ((reach + C - 1) / C * C + BT_ROWS - 1) / BT_ROWS;
@@ -1037,7 +1037,7 @@ spmv_status spmv_jds_from_csr(int32_t n, int64_t nnz, const int32_t *row_ptr, co
     } else {
         SPMV_HIP(hipMemsetAsync(jd_ptr, 0, sizeof(int32_t), s));
     }
-    if (nnz > 0) {
+    if (nnz > 0 && ndiag > 0) {          // row_ptr may hold no entries whatever nnz says
         JtArgs t{};
         t.rp = row_ptr;
         t.perm = perm;
