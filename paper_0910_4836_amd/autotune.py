@@ -252,7 +252,7 @@ def tune_crs(tuner: "Autotuner", A: S.CSR, x: torch.Tensor, longest: int,
     caller): entries per block, and whether the gathers go in entry order
     (spmv_crs) or row order (spmv_crs_staged).  A's plan is rebuilt with the
     choice and A.staged set; the block size is returned."""
-    sig = "crs2:" + signature(A.n_rows, longest, A.nnz)
+    sig = "crs3:" + signature(A.n_rows, longest, A.nnz)
     ent = tuner.cache.get(_device_key(), {}).get(sig)
     if ent is None:
         timings = {}

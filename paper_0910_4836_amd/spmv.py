@@ -105,7 +105,8 @@ class CSR:
     plan: Optional[torch.Tensor] = None
     n_blocks: int = 0
     block_nnz: int = 0
-    staged: bool = False        # spmv_crs runs the staged kernel (spmv_crs_staged) over the plan
+    staged: Optional[bool] = None   # spmv_crs over the plan: True the staged kernel (spmv_crs_staged), False the
+                                    # entry-order one (spmv_crs), None the one that the rows favour
     longest: int = -1           # entries of the longest row, once a plan has been built
 
     @property
@@ -406,7 +407,7 @@ def _out_vec(y, n, x, beta, n_cols):
     return y
 
 
-# The staged kernel without being asked for: blocks of 1,024 entries whose rows
+# The staged kernel where A.staged is None: blocks of 1,024 entries whose rows
 # are short and get at least four lanes each (16 entries per row on average).
 # Against the plain kernel 1.00 to 1.35 times as fast (banded rows of 20, 4 M:
 # FP32 439 and 356 us, FP64 544 and 442; rows of 5 to 40, 300 k: 41 and 36;
@@ -417,14 +418,17 @@ CRS_STAGED_LONGEST, CRS_STAGED_MEAN = 64, 16
 
 
 def _crs_staged(A: CSR) -> bool:
-    return A.staged or (0 < A.longest <= CRS_STAGED_LONGEST and A.block_nnz in (0, 1024)
-                        and A.nnz >= CRS_STAGED_MEAN * A.n_rows)
+    if A.staged is not None:
+        return A.staged
+    return (0 < A.longest <= CRS_STAGED_LONGEST and A.block_nnz in (0, 1024)
+            and A.nnz >= CRS_STAGED_MEAN * A.n_rows)
 
 
 def spmv_crs(A: CSR, x: torch.Tensor, y: Optional[torch.Tensor] = None, alpha: float = 1.0, beta: float = 0.0,
              use_plan: bool = True) -> torch.Tensor:
     """y = alpha*A x + beta*y with the CRS kernels (spmv_crs; spmv_crs_staged
-    when the plan is used and A.staged is set or its rows favour it)."""
+    over the plan where A.staged says so, or where it says nothing and the
+    rows favour it)."""
     y = _out_vec(y, A.n_rows, x, beta, A.n_cols)
     if use_plan and A.plan is None:
         spmv_crs_plan(A)
