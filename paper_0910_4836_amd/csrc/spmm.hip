@@ -460,12 +460,25 @@ struct MmPlan {
     int32_t short_runs;     // workgroups go to the XCDs in runs of 2, not 16
 };
 
+constexpr int VMCNT_0 = 0x0f70;            // s_waitcnt vmcnt(0), the other counters free
+
 // One lane's share of a JDS row for the interleaved multi-vector kernel:
 // columns j, j + LPR, ..., j + (CPL-1)*LPR over diagonals sub, sub + GPR, ...
 // of row r, U per trip, stopping (for the whole wavefront) where the
 // wavefront's first and longest row r_first ends.  Column t*LPR + j of the
 // row's LPR lanes is one contiguous run of LPR elements per load.
-template <int LPR, int CPL, int U, bool WIDE, typename VT, typename XT>
+//
+// FEW: rows of X of a few lanes, 16 to 64 matrix rows per wavefront, whose
+// gathers are nearly all line fills once X is larger than the L2.  Then a
+// wavefront reads half a line of col and of val per diagonal (LPR = 4), its
+// neighbour the other half; loaded without the streaming hint the line is still
+// in the L1 by then.  IN_TURN: each of a trip's gathers waits for the one
+// before; two at a time push such lines out.  FP32, 1.5 M rows, 3 vectors, with
+// the hint and two at a time, without the hint, and in turn as well: rows of 5
+// to 40 anywhere 538, 520 and 399 us; power law 331, 312 and 308; banded 217,
+// 213 and 221; 300 k rows: 78, 56 and 55; 134, 110 and 126; 53, 43 and 46.
+// FP64, one vector, 160 k banded rows: 20.9, 16.9 and 15.9.
+template <int LPR, int CPL, int U, bool FEW, bool IN_TURN, bool WIDE, typename VT, typename XT>
 __device__ __forceinline__ void mm_jds_sum(const int32_t *__restrict__ jp, int32_t dlim,
                                            const int32_t *__restrict__ col, const VT *__restrict__ val,
                                            const XT *__restrict__ Xr, int32_t ld, int32_t k, int j, int32_t r,
@@ -488,17 +501,19 @@ __device__ __forceinline__ void mm_jds_sum(const int32_t *__restrict__ jp, int32
                 const int32_t off = jp[dd];
                 if (r < jp[dd + 1] - off) {
                     act[u] = true;
-                    c[u] = ld_stream(col + off + r);
-                    v[u] = ld_stream(val + off + r);
+                    c[u] = FEW ? col[off + r] : ld_stream(col + off + r);
+                    v[u] = FEW ? val[off + r] : ld_stream(val + off + r);
                 }
             }
         }
         XT xv[U][CPL];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u) {
+            if (IN_TURN && u > 0) __builtin_amdgcn_s_waitcnt(VMCNT_0);
 #pragma unroll
             for (int t = 0; t < CPL; ++t)
                 xv[u][t] = (act[u] && t * LPR + j < k) ? Xr[(int64_t)c[u] * ld + t * LPR + j] : XT(0);
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (act[u]) {
@@ -530,6 +545,7 @@ __global__ __launch_bounds__(NT) void spmm_jds_il_kernel(int32_t ndiag, const in
     // wavefronts are in flight (250 k power-law rows, 40 vectors, FP64: 349 us
     // with 2, 314), until they take too many registers (64, FP32: 282 with 2, 316)
     constexpr int U = SMALL && CPL < 8 ? 4 : 2;
+    constexpr bool FEW = K2 <= (sizeof(XT) == 4 ? 4 : 1), IN_TURN = FEW && !SMALL;
     __shared__ double part[NG][K2];
     // workgroups in runs of 16 per XCD: neighbouring rows' lines meet in one L2
     // (2 M power-law rows, 8 vectors, FP32: in turn 730 us, runs of 4 689, 16
@@ -569,11 +585,11 @@ __global__ __launch_bounds__(NT) void spmm_jds_il_kernel(int32_t ndiag, const in
     }
     double td[CPL];
     if (jp_lds) {
-        if (F64 || wide) mm_jds_sum<LPR, CPL, U, true, VT, XT>(jp_s, dlim, col, val, Xr, ld, k, j, r, ok, r_first, sub * D + dl, GPR * D, td);
-        else mm_jds_sum<LPR, CPL, U, false, VT, XT>(jp_s, dlim, col, val, Xr, ld, k, j, r, ok, r_first, sub * D + dl, GPR * D, td);
+        if (F64 || wide) mm_jds_sum<LPR, CPL, U, FEW, IN_TURN, true, VT, XT>(jp_s, dlim, col, val, Xr, ld, k, j, r, ok, r_first, sub * D + dl, GPR * D, td);
+        else mm_jds_sum<LPR, CPL, U, FEW, IN_TURN, false, VT, XT>(jp_s, dlim, col, val, Xr, ld, k, j, r, ok, r_first, sub * D + dl, GPR * D, td);
     } else {
-        if (F64 || wide) mm_jds_sum<LPR, CPL, U, true, VT, XT>(jp, dlim, col, val, Xr, ld, k, j, r, ok, r_first, sub * D + dl, GPR * D, td);
-        else mm_jds_sum<LPR, CPL, U, false, VT, XT>(jp, dlim, col, val, Xr, ld, k, j, r, ok, r_first, sub * D + dl, GPR * D, td);
+        if (F64 || wide) mm_jds_sum<LPR, CPL, U, FEW, IN_TURN, true, VT, XT>(jp, dlim, col, val, Xr, ld, k, j, r, ok, r_first, sub * D + dl, GPR * D, td);
+        else mm_jds_sum<LPR, CPL, U, FEW, IN_TURN, false, VT, XT>(jp, dlim, col, val, Xr, ld, k, j, r, ok, r_first, sub * D + dl, GPR * D, td);
     }
     // the D groups of a row: fixed xor tree
     if (SMALL)
