@@ -395,7 +395,9 @@ spmv_status spmv_dot_noalloc(int64_t n, const void *x, const void *y, spmv_dtype
  * ws (spmm_workspace_size(n_cols, k, vec_dt) bytes, may be NULL): with it,
  * X is first copied into an interleaved row-major block inside ws so that
  * every entry gathers its k values contiguously (k <= 64); without it the
- * kernels gather straight from the column-major X.  Same arithmetic rules as
+ * kernels gather straight from the column-major X.  The library pads the
+ * block's rows where that pays; a workspace of k elements per row of X, rounded
+ * up to 256 bytes, and 256 more is taken too, without padding.  Same arithmetic rules as
  * the single-vector forms.  spmm_crs takes the spmv_crs_plan row blocks and
  * the block_nnz they were built with (0 = default; on the workspace path a
  * multi-row block's val/col are staged in LDS, block_nnz of each); spmm_jds

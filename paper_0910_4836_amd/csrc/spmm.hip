@@ -917,11 +917,11 @@ static MmPlan plan_mm_jds(int32_t n, const int32_t *h_jd_ptr, int32_t ndiag, boo
     return P;
 }
 
-// Stride of the staged rows, in elements.  Rows of 41 to 127 bytes are padded
-// to 64 or 128, so that each lies in one 128-byte line: what the gathers fetch
-// is lines, and an unpadded row of 52 bytes (13 FP32 columns) is in two of
-// them for 40% of the entries, one of 104 bytes for 80% (JDS, 1 M power-law
-// rows, k = 13: FP32 482 to 435 us, FP64 631 to 480).  Shorter
+// Stride of the staged rows, in elements, where they are padded.  Rows of 41
+// to 127 bytes to 64 or 128, so that each lies in one 128-byte line: what the
+// gathers fetch is lines, and an unpadded row of 52 bytes (13 FP32 columns) is
+// in two of them for 40% of the entries, one of 104 bytes for 80% (JDS, 1 M
+// power-law rows, k = 13: FP32 482 to 435 us, FP64 631 to 480).  Shorter
 // rows straddle less than the padding adds (k = 9, FP32, 36 bytes: 1 M
 // power-law rows 403 to 393 us, 80 k banded rows 34.7 and 37.5), and above a line
 // the padding moves more than it saves (20 FP64 columns to 256 bytes: 611 to
@@ -933,6 +933,31 @@ static int32_t mm_padded_ld(int32_t k, size_t elem)
     return (int32_t)(row / elem);
 }
 
+// The stride that a product takes.  A padded X is larger, and that is all it is
+// while the L2s hold X: the larger X, the more of its gathers are line fills,
+// and the more padding they pay for.  Measured with rows of 44 to 124 bytes,
+// banded, uniform and power-law matrices of 20 k to 1 M rows, padded and not:
+//   JDS and blocked JDS gain where the padding adds less than one part in 14
+//   MB / X (17 FP32 columns to 32: 20 k rows 17.1 us, padded 20.0, windowed 21.3
+//   and 28.7; 60 k 45.2 and 44.5; 150 k 108 and 98; 31 to 32: 20 k rows 28.8
+//   and 25.5);
+//   CRS takes the rows in their own order, neighbours share more lines, and
+//   it gains from twice that on (11 FP32 columns to 16: 80 k rows 46 and 54
+//   us, 200 k 112 and 113, 1 M 536 and 464).
+// Where a row of X is gathered eight times or less, writing it out padded costs
+// more than the gathers gain back (7-point stencil, 1 M rows: JDS, 9 FP64
+// columns 160 and 188 us, CRS, 17 FP32 columns 141 and 192).
+enum MmReuse { MM_REUSE_JDS, MM_REUSE_CRS };
+constexpr int64_t MM_PAD_X = 14000000;
+constexpr int64_t MM_PAD_ENTRIES = 8;
+
+static int32_t mm_staged_ld(int64_t n_cols, int32_t k, size_t elem, MmReuse reuse, int64_t entries)
+{
+    const int64_t ld = mm_padded_ld(k, elem), bytes = n_cols * ld * (int64_t)elem;
+    if (entries <= MM_PAD_ENTRIES * n_cols) return k;
+    return (ld - k) * (reuse == MM_REUSE_CRS ? 2 * MM_PAD_X : MM_PAD_X) <= k * bytes ? (int32_t)ld : k;
+}
+
 static size_t mm_ws_bytes(int32_t n_cols, int32_t ld, size_t elem)
 {
     return align_up((size_t)n_cols * (size_t)ld * elem, 256) + 256;
@@ -940,10 +965,10 @@ static size_t mm_ws_bytes(int32_t n_cols, int32_t ld, size_t elem)
 
 // The row-major block the interleaved kernels read: X itself for k = 1,
 // otherwise Xr in the workspace, filled here.  A workspace of the unpadded
-// rows' size is taken, without the padding.
+// rows' size is taken, without the padding.  want: the stride, mm_staged_ld.
 template <typename T>
-static spmv_status stage(int32_t n, int32_t k, const void *X, int64_t ldx, void *ws, size_t ws_bytes, const void **Xr,
-                         int32_t *ld, hipStream_t s)
+static spmv_status stage(int32_t n, int32_t k, const void *X, int64_t ldx, void *ws, size_t ws_bytes, int32_t want,
+                         const void **Xr, int32_t *ld, hipStream_t s)
 {
     if (k == 1) {
         *Xr = X;
@@ -951,8 +976,7 @@ static spmv_status stage(int32_t n, int32_t k, const void *X, int64_t ldx, void 
         return SPMV_OK;
     }
     *Xr = ws;
-    *ld = mm_padded_ld(k, sizeof(T));
-    if (ws_bytes < mm_ws_bytes(n, *ld, sizeof(T))) *ld = k;
+    *ld = ws_bytes < mm_ws_bytes(n, want, sizeof(T)) ? k : want;
     if (n == 0) return SPMV_OK;
     const int64_t rows = STAGE_ELEMS / k;              // 2 <= k <= MM_MAX_K2 = 64
     stage_rowmajor_kernel<T><<<(unsigned)ceil_div(n, rows), STAGE_THREADS, 0, s>>>(n, k, (const T *)X, ldx, (T *)ws, *ld);
@@ -1061,8 +1085,11 @@ spmv_status spmm_crs(int32_t n_rows, int32_t n_cols, const int32_t *row_ptr, con
     if (n_blocks == 0) return SPMV_OK;
     const void *Xr = nullptr;
     int32_t ld = k;
-    spmv_status st = vec_dt == SPMV_F64 ? stage<double>(n_cols, k, X, ldx, ws, ws_bytes, &Xr, &ld, s)
-                                        : stage<float>(n_cols, k, X, ldx, ws, ws_bytes, &Xr, &ld, s);
+    // a block holds at most block_nnz entries, and nearly that many where rows are short
+    const int32_t want = mm_staged_ld(n_cols, k, dtype_size(vec_dt), MM_REUSE_CRS,
+                                      (int64_t)n_blocks * block_nnz);
+    spmv_status st = vec_dt == SPMV_F64 ? stage<double>(n_cols, k, X, ldx, ws, ws_bytes, want, &Xr, &ld, s)
+                                        : stage<float>(n_cols, k, X, ldx, ws, ws_bytes, want, &Xr, &ld, s);
     if (st != SPMV_OK) return st;
     const int K2v = k2_for(k, vec_dt == SPMV_F64 ? 16 : 8);
 #define CRS_IL(VDT, VT, XDT, XT)                                                                              \
@@ -1104,8 +1131,9 @@ spmv_status spmm_jds(int32_t n, int32_t n_cols, const int32_t *perm, const int32
     SPMV_REQUIRE(ws_bytes >= mm_ws_bytes(n_cols, k, dtype_size(vec_dt)), "spmm_jds: workspace too small");
     const void *Xr = nullptr;
     int32_t ld = k;
-    spmv_status st = vec_dt == SPMV_F64 ? stage<double>(n_cols, k, X, ldx, ws, ws_bytes, &Xr, &ld, s)
-                                        : stage<float>(n_cols, k, X, ldx, ws, ws_bytes, &Xr, &ld, s);
+    const int32_t want = mm_staged_ld(n_cols, k, dtype_size(vec_dt), MM_REUSE_JDS, h_jd_ptr[ndiag]);
+    spmv_status st = vec_dt == SPMV_F64 ? stage<double>(n_cols, k, X, ldx, ws, ws_bytes, want, &Xr, &ld, s)
+                                        : stage<float>(n_cols, k, X, ldx, ws, ws_bytes, want, &Xr, &ld, s);
     if (st != SPMV_OK) return st;
     const int K2v = k2_for(k);
     const int sym = (flags & SPMV_SYMPERM) ? 1 : 0;
@@ -1170,8 +1198,10 @@ spmv_status spmm_jds_blocked(int32_t n, int32_t n_cols, const int32_t *perm, int
     hipStream_t s = as_stream(stream);
     const void *Xr = nullptr;
     int32_t ld = k;
-    spmv_status st = vec_dt == SPMV_F64 ? stage<double>(n_cols, k, X, ldx, ws, ws_bytes, &Xr, &ld, s)
-                                        : stage<float>(n_cols, k, X, ldx, ws, ws_bytes, &Xr, &ld, s);
+    // the number of entries is not known here: a caller with few brings the smaller workspace
+    const int32_t want = mm_staged_ld(n_cols, k, dtype_size(vec_dt), MM_REUSE_JDS, INT64_MAX);
+    spmv_status st = vec_dt == SPMV_F64 ? stage<double>(n_cols, k, X, ldx, ws, ws_bytes, want, &Xr, &ld, s)
+                                        : stage<float>(n_cols, k, X, ldx, ws, ws_bytes, want, &Xr, &ld, s);
     if (st != SPMV_OK) return st;
     if (grid == 0) return SPMV_OK;
     const int K2v = k2_for(k);
