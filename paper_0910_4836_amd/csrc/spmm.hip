@@ -439,14 +439,23 @@ __global__ __launch_bounds__(NT) void spmm_crs_il_kernel(const int32_t *__restri
 // k = 8, FP32: 734 us at D = 1, 861 with D <= 4 and no class split finer than
 // 32 diagonals).  Between MM_TINY_ROWS and MM_SMALL_ROWS half as many groups
 // (250 k rows, k = 8: D <= 4 106 us, D <= 8 124, D = 1 190).
-// Where no row is long, it pays for few vectors or very few rows only (74 k
-// rows of 5 to 40, FP32: 2 vectors 19 and 21 us, 3 24 and 21, 6 31 and 34, 40
-// vectors 86 and 100; 20 k rows, 12 vectors: 19.5 to 16.3).
+// Where no row is long, splitting evens out rows of different lengths and fills
+// a chip that the launch does not.  Not split and split, times of one over the
+// other, rows of 5 to 40 and of 20 entries each: 8 lanes per row (5 vectors
+// and more; 8 vectors here): 20 k rows, FP32 1.18 and 1.10, FP64 1.14 and 1.27; 45 k
+// 1.08 and 0.99, 1.07 and 0.97; 60 k 1.00 and 0.97, 1.00 and 0.95; 149 k 0.90
+// and 1.03, 0.93 and 1.06: up to MM_FEW_ROWS.  4 lanes per row are half the
+// wavefronts for the same rows and gain for longer: 60 k rows, FP32 1.24 and
+// 1.21, FP64 1.11 and 1.01; 110 k 1.03 and 0.98, 1.03 and 1.10; 149 k 0.96 and
+// 1.14, 1.02 and 1.09; 290 k 0.91 and 1.07, 0.92 and 1.06 (7-point stencil, 290
+// k: 1.14 and 1.04): up to MM_SMALL_ROWS.  1 and 2 lanes go up and down with how
+// the launch divides among the CUs (149 k rows, one vector: 0.73 and 1.16).
 constexpr int64_t MM_SMALL_ROWS = 300000;
 constexpr int64_t MM_TINY_ROWS = 150000;
-static bool mm_small(int64_t n, int64_t longest, int k)
+constexpr int64_t MM_FEW_ROWS = 60000;
+static bool mm_small(int64_t n, int64_t longest, int lanes_per_row)
 {
-    return n < MM_SMALL_ROWS && (longest > 64 || k == 3 || k == 4 || n < 60000);
+    return n < MM_SMALL_ROWS && (longest > 64 || lanes_per_row == 4 || n < MM_FEW_ROWS);
 }
 struct MmClass {
     int32_t wg_end, row_start, row_end, gpr;
@@ -1004,7 +1013,7 @@ static void launch_jds_il(int32_t n, const int32_t *h_jd_ptr, int32_t ndiag, con
                           int64_t ldy, double alpha, double beta, hipStream_t s)
 {
     constexpr int NT = MM_JDS_THREADS;
-    const bool small = mm_small(n, ndiag, k);
+    const bool small = mm_small(n, ndiag, mm_jds_lpr<K2, XT>());
     const MmPlan P = plan_mm_jds(n, h_jd_ptr, ndiag, small, NT / mm_jds_lpr<K2, XT>(), NT / WAVE);
     if (P.ncls == 0) return;
     // room for the longest jd_ptr prefix a class stages (dlim + 1 <= min(ndiag + 1, MM_JP_LDS))
