@@ -105,30 +105,41 @@ class Autotuner:
         self.cache.setdefault(_device_key(), {})[sig] = ent
         _store(self.cache_path, self.cache)
 
-    def tune_batched(self, jds_list: Sequence[S.JDS], sample: int = 16) -> Tuple[int, int, int]:
+    def tune_batched(self, jds_list: Sequence[S.JDS], sample: int = 16,
+                     n_workgroups: int = 0) -> Tuple[int, int, int]:
         """Best (C, R, U) for a batch of matrices sharing one signature: builds
         the blocked layout of up to `sample` of them for each C and times the
-        persistent launch for each (R, U)."""
-        sig = "batched:" + self._batch_signature(jds_list)
+        launch of n_workgroups for each (R, U) of the plain form and, where no
+        number of workgroups is given, the staged form (U = 0) at 64 rows per
+        wavefront."""
+        sig = f"batched2:{f'wg{n_workgroups}:' if n_workgroups else ''}" + self._batch_signature(jds_list)
         hit = self.lookup(sig, ("C", "R", "U"))
         if hit is not None:
             return hit
         pick = list(jds_list[:: max(1, len(jds_list) // sample)])[:sample]
         timings: Dict[Tuple[int, int, int], float] = {}
+        staged: Dict[Tuple[int, int, int], float] = {}
+        # 0 rows per wavefront are 64 here
+        rs = [R for R in self.rs if R or 64 not in self.rs]
         xs = [torch.rand(J.n_cols, dtype=torch.float32, device=J.jd_val.device) for J in pick]
         x = torch.cat(xs)
         for C in self.cs:
             mats = [S.jds_blocked_from_jds(J, C) for J in pick]
-            for R in self.rs:
-                Bt = S.Batched(mats, rows_per_wave=R)
+            for R in rs:
+                Bt = S.Batched(mats, rows_per_wave=R, n_workgroups=n_workgroups)
                 y = torch.empty(Bt.total_rows, dtype=torch.float32, device=x.device)
                 for U in self.us:
                     Bt.unroll = U
                     timings[(C, R, U)] = _time(lambda: Bt(x, y))
+                if R in (0, 64) and n_workgroups == 0:
+                    Bt.unroll = 0
+                    staged[(C, R, 0)] = _time(lambda: Bt(x, y))
             del mats
-        best = min(timings, key=timings.get)
         self.log.append({"signature": sig, "timings_ms": {f"C{c}_R{r}_U{u}": round(t, 5)
-                                                          for (c, r, u), t in timings.items()}})
+                                                          for (c, r, u), t in timings.items()},
+                         "staged_ms": {f"C{c}": round(t, 5) for (c, _, _), t in staged.items()}})
+        timings.update(staged)
+        best = min(timings, key=timings.get)
         self._record(sig, ("C", "R", "U"), best, timings)
         return best
 
@@ -336,6 +347,6 @@ def build_batched(jds_list: Sequence[S.JDS], tuner: Autotuner = None, n_workgrou
     """Blocked layouts and the persistent plan for many matrices, with the
     slice height / rows per wavefront / unroll the autotuner picks."""
     tuner = tuner or Autotuner()
-    C, R, U = tuner.tune_batched(jds_list)
+    C, R, U = tuner.tune_batched(jds_list, n_workgroups=n_workgroups)
     mats = [S.jds_blocked_from_jds(J, C) for J in jds_list]
     return S.Batched(mats, rows_per_wave=R, unroll=U, n_workgroups=n_workgroups)

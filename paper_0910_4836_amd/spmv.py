@@ -1172,8 +1172,9 @@ class Batched:
 
     ``mats`` is a list of Blocked matrices (float32 values).  Their arrays are
     concatenated once; x and y of all matrices are concatenated in order.
-    With 64 rows per wavefront and no number of workgroups given, x is staged
-    in LDS; otherwise unroll is the diagonals per trip of the plain form (0 = 4).
+    With 64 rows per wavefront (rows_per_wave 64 or 0) and neither unroll nor a
+    number of workgroups given, x is staged in LDS; otherwise the plain form
+    runs, with unroll diagonals per trip (2, 4 or 8; 0 = 4).
     """
 
     def __init__(self, mats, rows_per_wave: int = 64, unroll: int = 0, n_workgroups: int = 0):
@@ -1222,9 +1223,10 @@ class Batched:
     def __call__(self, x: torch.Tensor, y: Optional[torch.Tensor] = None) -> torch.Tensor:
         if y is None:
             y = torch.empty(self.total_rows, dtype=torch.float32, device=x.device)
-        staged = self.rows_per_wave in (0, 64) and self.n_workgroups == 0
+        # unroll 0 with no number of workgroups is the library's staged form, made for 64 rows per wavefront
+        unroll = self.unroll if self.rows_per_wave in (0, 64) else self.unroll or 4
         call("spmv_batched", self.n_tiles, _p(self.plan), _p(self.perm), _p(self.bl_col), _p(self.bl_val), _p(x),
-             _p(y), 0 if staged else self.unroll or 4, self.n_workgroups, _stream())
+             _p(y), unroll, self.n_workgroups, _stream())
         return y
 
 
