@@ -429,7 +429,7 @@ def load_powerlaw(torch, sp, dev, tune_cache=""):
     timed("row_split_blocked_parts_ms", lambda: RS.blocked_parts(bC))
     wS, wC, wU, wW = timed("autotune_windowed_ms", lambda: tuner.tune_windowed(A, xd, J.ndiag))
     BW = timed("jds_blocked_windowed_from_csr_ms", lambda: sp.jds_blocked_windowed_from_csr(A, wC, wS))
-    timed("windowed_tile_plan_ms", lambda: sp.spmv_jds_blocked_tiles(BW, 32, 0, wW))
+    timed("windowed_tile_plan_ms", lambda: sp.spmv_jds_blocked_tiles(BW, 0, 0, wW))
     host = (r, c, v, n, x)
     tune = {"crs_block_nnz": crs_bn, "crs_staged": A.staged, "jds_unroll": jds_u, "jds_max_iters": jds_mi, "jds_wg_waves": jds_w,
             "jds_tiled": jds_tiled, "blocked_C": bC, "blocked_rows_per_wave": bR, "blocked_unroll": bU,
@@ -495,8 +495,7 @@ def powerlaw_kernels(sp, W, torch):
     ]
     BW = W["BW"]
     wU, wW = T["windowed_unroll"], T["windowed_wg_waves"]
-    ks += [("blocked_windowed_f64", lambda: sp.spmv_jds_blocked_tiled(BW, x, y, unroll=wU, max_iters=32,
-                                                                       wg_waves=wW))]
+    ks += [("blocked_windowed_f64", lambda: sp.spmv_jds_blocked_tiled(BW, x, y, unroll=wU, wg_waves=wW))]
     bmin = {
         "blocked_windowed_f64": bytes_blocked(nnz, n, n, BW.n_slices, 8, 8),
         "crs_f64": bytes_crs(nnz, n, n, 8, 8),
