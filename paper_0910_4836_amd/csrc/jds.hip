@@ -934,7 +934,12 @@ static void plan_tiles_local(int32_t n, int32_t U, int64_t n_units, F unit_len, 
     // power-law rows, FP64), 114, 111 and 123 (700 k), 19.8, 16.9 and 17.9 (60
     // k, blocked, FP32).  Where no row is long there are too few to share out
     // evenly in runs (300 k rows of at most 26: 20.5 us, 23.4 in fours).
-    const size_t run = n_units == 0 || unit_len(0) <= 32 ? 1 : n >= 1500000 ? 16 : 4;
+    // Fours and sixteens, power-law rows, FP64: JDS 1 M rows 150 and 155 us,
+    // 1.5 M 254 and 262, 1.75 M 289 and 289, 2 M 343 and 334, 3 M 561 and 555 (FP32
+    // 108 and 115, 169 and 174, 220 and 220, 248 and 243, 409 and 403); blocked
+    // 1 M 134 and 130, 1.5 M 222 and 218, 1.75 M 270 and 263, 2 M 319 and 319
+    // (FP32 the same within 1.5%).
+    const size_t run = n_units == 0 || unit_len(0) <= 32 ? 1 : n >= (U == 1 ? 1750000 : 1500000) ? 16 : 4;
     std::vector<double> cost(ceil_div(others.size(), run), 0.0);
     std::vector<int64_t> order(cost.size());
     for (size_t t = 0; t < others.size(); ++t) cost[t / run] += others[t].cost;
@@ -1004,6 +1009,10 @@ static spmv_status launch_jds(const JdsArgs &a, const JdsPlan &P, int unroll, sp
 // than 5%.  Class plans of large matrices of short rows keep that choice: they
 // have no XCD locality, and 16 wavefronts of neighbouring rows share their x
 // lines in L1 (banded, 1.5 M rows, blocked FP32: 16 wavefronts 108, 4 116 us).
+// So do JDS tile plans of very large ones whose rows are long enough to split
+// (rows of 5 to 40, FP32, former choice and 4 wavefronts: 1.5 M rows 317 and
+// 294 us, 2 M 455 and 468, 2.5 M 632 and 665, 4 M 1207 and 1260; FP64 467 and
+// 460, 658 and 671, 857 and 884, 1499 and 1531).
 struct JdsShape {
     int unroll, max_iters, waves;
 };
@@ -1012,6 +1021,7 @@ static JdsShape jds_shape(bool blocked, bool tiles, bool windowed, int64_t n, in
 {
     if (longest <= 64) {
         if (n < 100000) return {8, 8, 4};
+        if (tiles && !blocked && n >= 2000000 && longest > 32) return {4, JDS_DEFAULT_MAX_ITERS, 16};
         if (!tiles && n >= 1000000 && (!blocked || !x8)) return {4, JDS_DEFAULT_MAX_ITERS, 16};
         return blocked ? JdsShape{8, JDS_DEFAULT_MAX_ITERS, 4} : JdsShape{4, 64, 4};
     }
