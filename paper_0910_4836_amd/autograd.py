@@ -186,7 +186,10 @@ class ChebyshevLoss(torch.autograd.Function):
         op, K, ckpt, saved = ctx.op, ctx.steps, ctx.ckpt, ctx.saved
         scale = float(gl.item()) if gl.numel() == 1 else 1.0
         n = x.numel()
-        # adjoint states bar[k]; only three are live at a time
+        # adjoint states bar[k]: the recurrence needs three at a time.  A segment's are
+        # kept until its value gradients are summed, up to GRAD_MAX_PAIRS more, and the
+        # sum stages that many states (a power of two) side by side: with the default
+        # checkpoint 5 or 6 adjoints and 8 staged states, 13 or 14 vectors of n in all
         bar = {K: S.spmv_axpby(2.0 * scale, y_last, 0.0, torch.empty_like(y_last))}
         # in the vectors' type, which the products compute in, rounded to the values' at the end
         dvals = torch.empty(op.nnz, dtype=x.dtype, device=vals.device)

@@ -1013,6 +1013,16 @@ static spmv_status launch_jds(const JdsArgs &a, const JdsPlan &P, int unroll, sp
 // (rows of 5 to 40, FP32, former choice and 4 wavefronts: 1.5 M rows 317 and
 // 294 us, 2 M 455 and 468, 2.5 M 632 and 665, 4 M 1207 and 1260; FP64 467 and
 // 460, 658 and 671, 857 and 884, 1499 and 1531).
+// The lines, first choice over second, below and above (FP64, FP32):
+//   100 k, no row long: JDS, rows of 5 to 40, 80 k 1.02, 0.91, 110 k 1.16,
+//     1.16; diagonals 0.86, 0.83, 1.14, 0.99; blocked 0.76, 0.67 and 0.76, 0.84.
+//   300 k, blocked: 16 and 8 wavefronts, power law, tile plans 250 k 0.89, 0.99,
+//     350 k 1.09, 1.16; class plans 1.30, 1.34 and 1.04, 1.07.
+//   700 k: 16 and 32 diagonals, JDS 600 k 0.86, 0.77, 800 k 0.98, 1.00; 16 and 64,
+//     blocked tile plans 0.92, 0.95 and 0.95, 0.97, 1.1 M 1.05, 1.01 (class plans,
+//     whose workgroups go in runs, 0.89, 0.83 there still).
+//   1.75 M, JDS: 32 diagonals and 16 wavefronts to 64 and 4, tile plans 1.6 M
+//     1.08, 0.90, 1.9 M 1.11, 0.97, 2.4 M 1.12, 1.01.
 struct JdsShape {
     int unroll, max_iters, waves;
 };
