@@ -77,7 +77,8 @@ static CooSplit coo_split(int32_t n_rows, int32_t n_cols, int64_t nnz)
 
 // flags[0]: an index is out of range; flags[1]: rows out of bucket order.
 // Also the first radix pass's digit counts (skipped if counts is null), and
-// their totals over the tiles (skipped if totals is null).  FINE: flags[5] if a
+// their totals over the tiles (skipped if totals is null; flags[7] if one is
+// more than a bucket may hold).  FINE: flags[5] if a
 // tile out of bucket order holds more than `most` entries of one of COO_FINE
 // buckets.
 constexpr int COO_FINE = 2048;
@@ -136,7 +137,8 @@ __global__ __launch_bounds__(RS_THREADS) void coo_check_kernel(const int32_t *__
     if (!counts) return;
     for (int i = threadIdx.x; i < RS_BINS; i += RS_THREADS) {
         counts[(int64_t)i * ntiles + tile] = h[i];
-        if (totals && h[i]) atomicAdd(totals + i, h[i]);
+        // whoever adds last sees the whole bucket
+        if (totals && h[i] && atomicAdd(totals + i, h[i]) + h[i] > CB_MAX) flags[7] = 1;
     }
 }
 
@@ -156,7 +158,6 @@ __global__ __launch_bounds__(RS_THREADS) void coo_count_kernel(const int32_t *__
         if (i < n) atomicAdd(&h[((uint32_t)row[i] >> row_bits) & (COO_FINE - 1)], 1);
     }
     __syncthreads();
-    // whoever adds last sees the whole bucket
     int32_t most = 0;
     for (int i = threadIdx.x; i < COO_FINE; i += RS_THREADS)
         if (h[i]) most = max(most, atomicAdd(sizes + i, h[i]) + h[i]);
@@ -631,8 +632,8 @@ spmv_status spmv_csr_from_coo(int32_t n_rows, int32_t n_cols, int64_t nnz, const
     const CooSplit C = coo_split(n_rows, n_cols, nnz);
     const size_t tb = radix_table_bytes(nnz);
     const RadixTables R(nnz, wc.take<char>(tb), tb);
-    int32_t h[COO_FLAGS] = {0};
-    SPMV_HIP(hipMemsetAsync(flags, 0, sizeof(h), s));
+    int32_t h[COO_TOTALS] = {0};
+    SPMV_HIP(hipMemsetAsync(flags, 0, sizeof(int32_t) * (C.passes == 1 ? COO_FLAGS : COO_TOTALS), s));
     int32_t *counts = C.use && C.passes > 0 ? R.counts : nullptr;
     int32_t *totals = C.passes == 1 ? flags + COO_TOTALS : nullptr;
     const unsigned tiles = (unsigned)R.ntiles;
@@ -651,14 +652,14 @@ spmv_status spmv_csr_from_coo(int32_t n_rows, int32_t n_cols, int64_t nnz, const
     SPMV_HIP(hipStreamSynchronize(s));
     if (h[0]) return fail(SPMV_ERR_BAD_FORMAT, "spmv_csr_from_coo: row or column index out of range");
 
-    bool fits = C.use && *std::max_element(h + COO_TOTALS, h + COO_FLAGS) <= CB_MAX;
+    bool fits = C.use && h[7] == 0;
     if (fits && fine && h[1] && h[5]) {
         WsCarver tmp = wc;
         int32_t *sizes = tmp.take<int32_t>(COO_FINE);
         SPMV_HIP(hipMemsetAsync(sizes, 0, sizeof(int32_t) * COO_FINE, s));
         coo_count_kernel<<<tiles, RS_THREADS, 0, s>>>(row, nnz, C.row_bits, sizes, flags + 6);
         SPMV_CHECK_LAUNCH("coo count");
-        SPMV_HIP(hipMemcpyAsync(h, flags, sizeof(int32_t) * COO_TOTALS, hipMemcpyDeviceToHost, s));
+        SPMV_HIP(hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, s));
         SPMV_HIP(hipStreamSynchronize(s));
         fits = h[6] <= CB_MAX;
     }
@@ -671,7 +672,7 @@ spmv_status spmv_csr_from_coo(int32_t n_rows, int32_t n_cols, int64_t nnz, const
                 : coo_by_buckets<float, uint32_t>(C, n_rows, nnz, row, col, (const float *)val, ordered, R, flags,
                                                   row_ptr, col_idx, (float *)val_out, wc, s);
         if (st != SPMV_OK) return st;
-        SPMV_HIP(hipMemcpyAsync(h, flags, sizeof(int32_t) * COO_TOTALS, hipMemcpyDeviceToHost, s));
+        SPMV_HIP(hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, s));
         SPMV_HIP(hipStreamSynchronize(s));
         if (h[3] <= CB_MAX) {
             *h_nnz_out = h[4];
